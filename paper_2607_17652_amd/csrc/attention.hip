@@ -25,7 +25,7 @@
 //                  domain with lazy rescaling
 //   combine        merges split partials with their log-sum-exp weights,
 //                  walking the plan's list of split units
-//   attn_f32       a plain fp32 path (small problems, exactness reference)
+//   attn_f32       the same items in fp32 on v_mfma_f32_32x32x2_f32
 #include <type_traits>
 #include <utility>
 
@@ -41,6 +41,10 @@ constexpr int kRowsPerWg = 128;     // 4 waves x 32 query rows
 constexpr int kAttnThreads = 256;
 constexpr int kWgsPerCu = 3;          // resident attention workgroups per CU
 constexpr int kKeyTile = 32;
+constexpr int kF32WgsPerCu = 2;       // resident fp32 workgroups per CU
+// keys * head_dim that one fp32 workgroup walks without a plan: a key tile
+// takes it about D/32 us, the plan and the merge about 16
+constexpr long long kF32DirectWork = 32768;
 constexpr int kMinChunkTiles = 4;   // never split below 128 keys
 constexpr int kMaxSplits = 64;      // splits of one unit the combine can merge
 constexpr int kMaxHeadDim = 128;    // largest head_dim built (32, 64, 128)
@@ -1168,7 +1172,9 @@ combine_kernel(PackView pv, AttnWs ws, T* __restrict__ out, int Hq, int Hkv,
                 wgt[k][threadIdx.x] = w;
                 den += w;
             }
-            inv_den[threadIdx.x] = 1.0f / den;
+            // fp32: pieces of a skipped block hold -inf (its rows stay unwritten)
+            inv_den[threadIdx.x] = std::is_same<T, float>::value && mx == -INFINITY ? -1.0f
+                                                                                    : 1.0f / den;
         }
         __syncthreads();
     };
@@ -1176,6 +1182,7 @@ combine_kernel(PackView pv, AttnWs ws, T* __restrict__ out, int Hq, int Hkv,
         const int rr = e / per_row;
         const int d0 = (e % per_row) * 4;
         const float id = inv_den[rr];
+        if (std::is_same<T, float>::value && id < 0.f) return;
         const int r = rg * kRowsPerWg + rbase + rr;
         const int pos_local = r / g, hg = r % g;
         T* dst = out + ((size_t)(row0 + pos_local) * Hq + c * g + hg) * D + d0;
@@ -1256,97 +1263,277 @@ combine_kernel(PackView pv, AttnWs ws, T* __restrict__ out, int Hq, int Hkv,
 }
 
 // ---------------------------------------------------------------- fp32 ----
-// One workgroup per (tile, query head); each wave walks its rows with an
-// online softmax over 64-key chunks, one key per lane.
-constexpr int kF32MaxD = 256;
+// The same work items in fp32 on v_mfma_f32_32x32x2_f32: 4 waves x 32 query
+// rows, 32-key K and V^T tiles in two LDS buffers filled by direct
+// global->LDS loads.  A tile is D MFMAs of 64 cycles per wave, so the matrix
+// core is the bound by far: one tile of lead covers the loads, and two
+// workgroups per CU (64 KB of LDS each at D = 128) cover the softmax.
+//
+// Operands.  MFMA A/B lane l carries k-slot l/32, and a dot product does not
+// care which k goes into which slot: lane half h reads four consecutive d
+// (chunk 2j + h) in one 16-byte LDS read and feeds them to four MFMAs.  The
+// accumulator layout (rows (i/4)*8 + (l/32)*4 + i%4) then makes S^T value i
+// the P^T operand of the PV MFMA whose V^T operand is key chunk 2(i/4) + h,
+// element i%4: P never moves between lanes, and V^T is read the same way.
+//
+// DIRECT: one workgroup per unit over all its keys, no plan and no merge (for
+// caches too short to be worth splitting).
+//
+// Measured (8 requests of 256-2048 prefix keys, 16/4 heads, d = 128: 6.4
+// GFLOP, 42 us at the 154 TFLOP/s of a large fp32 matrix product): the whole
+// call takes 86 us with the plan and the merge, against 15.8 ms for one key
+// per lane on the vector units with K rows read a lane apart.
+template <int D>
+struct F32Tile {
+    static constexpr int kCpr = D / 4;                      // 16-byte chunks of a K row
+    static constexpr int kKCh = kKeyTile * kCpr;            // chunks of a K tile
+    static constexpr int kVCh = D * kKeyTile / 4;           // chunks of a V^T tile
+    static constexpr int kBytes = (kKCh + kVCh) * 16;       // one buffer
+    static constexpr int kLoads = kKCh / kAttnThreads;      // per thread: K, and as many V^T
+    static_assert(kKCh % kAttnThreads == 0 && kVCh == kKCh, "whole loads per workgroup");
+    // position of chunk c in row r: the 16 rows of one read hit 16 bank groups
+    __device__ static inline int kpos(int r, int c) { return c ^ (D == 32 ? (r >> 1) & 7 : r & 15); }
+    __device__ static inline int vpos(int d, int c) { return c ^ ((d >> 1) & 7); }
+};
 
-__global__ void __launch_bounds__(kAttnThreads)
+__device__ inline void dma4(const void* src, uint32_t lds_wave_base) {
+    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, off"
+                 :: "s"(lds_wave_base), "v"(src) : "memory");
+}
+
+template <int D, bool DIRECT>
+__global__ void __launch_bounds__(kAttnThreads, 2)
 attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k_cache,
                 const float* __restrict__ v_cache, const int32_t* __restrict__ page_table,
-                PackView pv, float* __restrict__ out, int Hq, int Hkv, int D, int bl,
-                int ps, int max_pages, int num_pages, float sm_scale) {
-    const int t = blockIdx.x;
-    const int hq = blockIdx.y;
-    if (t >= pv.hdr[kHdrTiles]) return;
-    const int32_t* tile = pv.tiles + (size_t)t * kTileInts;
+                PackView pv, AttnWs ws, float* __restrict__ out, int Hq, int Hkv, int g, int bl,
+                int RG, int ps, int ps_shift, int max_pages, int num_pages, float scale_log2,
+                PlanBounds bounds) {
+    using T = F32Tile<D>;
+    constexpr int NL = T::kLoads;
+    constexpr int DT = D / 32;
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
+    __shared__ __attribute__((aligned(16))) unsigned char buf[2 * T::kBytes];
+
+    int u, kb = 0, ke, slot = -1;
+    if (DIRECT) {
+        u = blockIdx.x;
+        if (u >= pv.hdr[kHdrTiles] * Hkv * RG) return;
+    } else {
+        const int32_t* it = ws.items + (size_t)blockIdx.x * kIItemInts;
+        u = it[kIUnit], kb = it[kIKb], ke = it[kIKe], slot = it[kISlot];
+        if ((int)blockIdx.x >= ws.counts[kCItems]) return;
+        if ((unsigned)u >= (unsigned)bounds.unit_cap || kb < 0 || (kb & (kKeyTile - 1)) != 0 ||
+            ke <= kb || (long long)ke > bounds.max_keys || slot < -1 || slot >= bounds.slot_cap) {
+            if (threadIdx.x == 0) record_error(pv.hdr, 0, FB_DERR_PLAN);
+            return;
+        }
+    }
+    const int rg = u % RG;
+    const int c = (u / RG) % Hkv;
+    const int32_t* tile = pv.tiles + (size_t)(u / (RG * Hkv)) * kTileInts;
     const int b = tile[kTB];
     const int row0 = tile[kTRow0];
     const int kv_len = tile[kTKvLen];
-    const int c = hq / (Hq / Hkv);
+    if (DIRECT) ke = kv_len;
     const int32_t* pt = page_table + (size_t)b * max_pages;
-    // Every page the tile reads must be valid, else the tile is skipped.
+
+    const int tid = threadIdx.x;
+    const int wave = tid >> 6;
+    const int lane = tid & 63;
+    const int n = lane & 31;
+    const int h = lane >> 5;
+    const int r_local = wave * 32 + n;
+    const int r = rg * kRowsPerWg + r_local;
+    const bool row_ok = r < bl * g;
+    const bool wave_ok = rg * kRowsPerWg + wave * 32 < bl * g;   // the wave has query rows
+
+    // Every page the block reads must be valid, else the block is skipped
+    // (a split block's pieces say so to the merge with a -inf weight).
     __shared__ int bad_page;
-    if (threadIdx.x == 0) bad_page = 0;
+    if (tid == 0) bad_page = 0;
     __syncthreads();
-    if ((long long)kv_len > (long long)max_pages * ps) {
-        if (threadIdx.x == 0) bad_page = 1;
+    if ((long long)kv_len > bounds.max_keys) {
+        if (tid == 0) bad_page = 1;
     } else {
-        for (int p = threadIdx.x; p * ps < kv_len; p += kAttnThreads) {
-            const int id = pt[p];
-            if (id < 0 || id >= num_pages) bad_page = 1;
-        }
+        const int n_pages = (kv_len + ps - 1) >> ps_shift;
+        for (int p = tid; p < n_pages; p += kAttnThreads)
+            if ((unsigned)pt[p] >= (unsigned)num_pages) bad_page = 1;
     }
     __syncthreads();
-    if (bad_page) {
-        if (threadIdx.x == 0) record_error(pv.hdr, b, FB_DERR_PAGE);
+    if (bad_page || ke > kv_len) {
+        if (tid == 0) record_error(pv.hdr, b, FB_DERR_PAGE);
+        if (slot >= 0 && tid < kRowsPerWg)
+            ws.part_lse[(size_t)slot * kRowsPerWg + tid] = -INFINITY;
         return;
     }
-    const int wave = threadIdx.x >> 6;
-    const int lane = threadIdx.x & 63;
-    constexpr int kAcc = kF32MaxD / 64;
 
-    for (int i = wave; i < bl; i += kAttnThreads / 64) {
-        const float* qrow = q + ((size_t)(row0 + i) * Hq + hq) * D;
-        float m = -INFINITY, l = 0.f;
-        float acc[kAcc];
+    const size_t q_off = row_ok ? ((size_t)(row0 + r / g) * Hq + c * g + r % g) * D : 0;
+    f32x4 qf[D / 8];   // chunk 2j + h of the lane's query row
 #pragma unroll
-        for (int j = 0; j < kAcc; ++j) acc[j] = 0.f;
-        for (int k0 = 0; k0 < kv_len; k0 += 64) {
-            const int key = k0 + lane;
-            float s = -INFINITY;
-            if (key < kv_len) {
-                const int page = pt[key / ps];
-                const float* krow = k_cache + (((size_t)page * Hkv + c) * ps + key % ps) * D;
-                float dot = 0.f;
-                for (int d = 0; d < D; ++d) dot = fmaf(qrow[d], krow[d], dot);
-                s = dot * sm_scale;
-            }
-            float cm = s;
+    for (int j = 0; j < D / 8; ++j)
+        qf[j] = row_ok ? *reinterpret_cast<const f32x4*>(q + q_off + (2 * j + h) * 4) : f32x4{};
+
+    // Loads: thread tid's load j fills LDS chunk j*256 + tid of each half of a
+    // buffer.  Keys past the item's end are read as its last key (their
+    // scores are masked, their V^T zeroed below).  A V^T chunk is four keys of
+    // one page; with pages of one or two keys V^T goes key by key instead.
+    const int n_tiles = (ke - kb + kKeyTile - 1) / kKeyTile;
+    const int vkc = T::vpos(tid >> 3, tid & 7);   // key chunk of the thread's V^T loads
+    const bool small_pages = ps < 4;
+    auto page_of = [&](int key) { return pt[min(key, ke - 1) >> ps_shift]; };
+    int pg_k[NL], pg_v = 0;
+    auto load_pages = [&](int i) {
+        const int key0 = kb + i * kKeyTile;
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) cm = fmaxf(cm, __shfl_xor(cm, off, 64));
-            const float m_new = fmaxf(m, cm);
-            const float alpha = expf(m - m_new);
-            const float p = key < kv_len ? expf(s - m_new) : 0.f;
-            float ps_sum = p;
+        for (int j = 0; j < NL; ++j) pg_k[j] = page_of(key0 + (j * kAttnThreads + tid) / T::kCpr);
+        pg_v = page_of(key0 + vkc * 4);
+    };
+    const uint32_t lds0 = (uint32_t)(uintptr_t)&buf[0];
+    auto issue = [&](int i) {
+        const int key0 = kb + i * kKeyTile;
+        const uint32_t base = lds0 + (i & 1) * T::kBytes;
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) ps_sum += __shfl_xor(ps_sum, off, 64);
-            l = l * alpha + ps_sum;
-#pragma unroll
-            for (int j = 0; j < kAcc; ++j) acc[j] *= alpha;
-            const int nk = min(64, kv_len - k0);
-            for (int jj = 0; jj < nk; ++jj) {
-                const float pj = __shfl(p, jj, 64);
-                const int kk = k0 + jj;
-                const int page = pt[kk / ps];
-                const float* vcol = v_cache + ((size_t)page * Hkv + c) * D * ps + kk % ps;
-#pragma unroll
-                for (int j = 0; j < kAcc; ++j) {
-                    const int d = lane + 64 * j;
-                    if (d < D) acc[j] = fmaf(pj, vcol[(size_t)d * ps], acc[j]);
-                }
-            }
-            m = m_new;
+        for (int j = 0; j < NL; ++j) {
+            const int s = j * kAttnThreads + tid;
+            const int kr = s / T::kCpr;
+            const int key = min(key0 + kr, ke - 1);
+            const float* src = k_cache +
+                (((size_t)pg_k[j] * Hkv + c) * ps + (key & (ps - 1))) * D +
+                T::kpos(kr, s % T::kCpr) * 4;
+            dma16(src, __builtin_amdgcn_readfirstlane(base + j * 4096 + wave * 1024));
         }
-        float* orow = out + ((size_t)(row0 + i) * Hq + hq) * D;
+        if (!small_pages) {
+            const int key = min(key0 + vkc * 4, (ke - 1) & ~3);
 #pragma unroll
-        for (int j = 0; j < kAcc; ++j) {
-            const int d = lane + 64 * j;
-            if (d < D) orow[d] = acc[j] / l;
+            for (int j = 0; j < NL; ++j) {
+                const int d = (j * kAttnThreads + tid) >> 3;
+                const float* src = v_cache + (((size_t)pg_v * Hkv + c) * D + d) * ps +
+                                   (key & (ps - 1));
+                dma16(src, __builtin_amdgcn_readfirstlane(base + T::kKCh * 16 + j * 4096 +
+                                                          wave * 1024));
+            }
+        } else {
+            for (int j = 0; j < NL * 4; ++j) {
+                const int s = j * kAttnThreads + tid;        // float of the V^T half
+                const int d = s >> 5;
+                const int key = min(key0 + T::vpos(d, (s >> 2) & 7) * 4 + (s & 3), ke - 1);
+                const float* src = v_cache + (((size_t)page_of(key) * Hkv + c) * D + d) * ps +
+                                   (key & (ps - 1));
+                dma4(src, __builtin_amdgcn_readfirstlane(base + T::kKCh * 16 + j * 1024 +
+                                                         wave * 256));
+            }
+        }
+    };
+
+    floatx16 o[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) o[dt] = floatx16{};
+    float m_run = -INFINITY;   // running max of scores, log2 domain (may lag by the slack)
+    float l = 0.f;             // this lane half's share of the denominator
+
+    load_pages(0);
+    issue(0);
+    if (n_tiles > 1) load_pages(1);
+    for (int i = 0; i < n_tiles; ++i) {
+        // tile i has landed and every wave is done with tile i - 1's buffer
+        wait_vm(0);
+        barrier_raw();
+        if (i + 1 < n_tiles) {
+            issue(i + 1);
+            if (i + 2 < n_tiles) load_pages(i + 2);
+        }
+        if (!wave_ok) continue;
+        const unsigned char* kt = buf + (i & 1) * T::kBytes;
+        const unsigned char* vt = kt + T::kKCh * 16;
+        const int valid = ke - kb - i * kKeyTile;   // keys of the tile below ke
+
+        floatx16 s = floatx16{};
+#pragma unroll
+        for (int j = 0; j < D / 8; ++j) {
+            const f32x4 kf = *reinterpret_cast<const f32x4*>(
+                kt + (n * T::kCpr + T::kpos(n, 2 * j + h)) * 16);
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+                s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[x], qf[j][x], s, 0, 0, 0);
+        }
+        if (valid < kKeyTile) {
+#pragma unroll
+            for (int x = 0; x < 16; ++x)
+                if ((x >> 2) * 8 + h * 4 + (x & 3) >= valid) s[x] = -INFINITY;
+        }
+        float mx = s[0];
+#pragma unroll
+        for (int x = 1; x < 16; ++x) mx = fmaxf(mx, s[x]);
+        mx = wave_xor32_max(mx) * scale_log2;
+        // rescale only when a row's max passes the running one by the slack
+        if (__any(mx > m_run + kRescaleSlack)) {
+            const float m_new = fmaxf(mx, m_run);
+            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+                for (int x = 0; x < 16; ++x) o[dt][x] *= alpha;
+            l *= alpha;
+            m_run = m_new;
+        }
+#pragma unroll
+        for (int x = 0; x < 16; ++x)
+            s[x] = __builtin_amdgcn_exp2f(fmaf(s[x], scale_log2, -m_run));
+        float t[8];
+#pragma unroll
+        for (int x = 0; x < 8; ++x) t[x] = s[x] + s[x + 8];
+        l += ((t[0] + t[4]) + (t[1] + t[5])) + ((t[2] + t[6]) + (t[3] + t[7]));
+#pragma unroll
+        for (int grp = 0; grp < 4; ++grp) {
+            f32x4 vf[DT];
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) {
+                const int d = dt * 32 + n;
+                vf[dt] = *reinterpret_cast<const f32x4*>(
+                    vt + (d * (kKeyTile / 4) + T::vpos(d, grp * 2 + h)) * 16);
+            }
+            if (valid < kKeyTile) {
+                // slots past ke may hold anything (even NaN)
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+                    if (grp * 8 + h * 4 + x >= valid)
+#pragma unroll
+                        for (int dt = 0; dt < DT; ++dt) vf[dt][x] = 0.f;
+            }
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt)
+                    o[dt] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[dt][x], s[grp * 4 + x], o[dt],
+                                                                0, 0, 0);
         }
     }
+    if (!wave_ok) return;
+
+    l += __shfl_xor(l, 32, 64);
+    const float inv_l = 1.0f / l;
+    if (slot < 0 && !row_ok) return;
+    float* dst = slot < 0 ? out + q_off
+                          : ws.part_o + ((size_t)slot * kRowsPerWg + r_local) * D;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int grp = 0; grp < 4; ++grp) {
+            const float4 v4 = make_float4(o[dt][grp * 4 + 0] * inv_l, o[dt][grp * 4 + 1] * inv_l,
+                                          o[dt][grp * 4 + 2] * inv_l, o[dt][grp * 4 + 3] * inv_l);
+            *reinterpret_cast<float4*>(dst + dt * 32 + grp * 8 + h * 4) = v4;
+        }
+    if (slot >= 0 && h == 0)
+        ws.part_lse[(size_t)slot * kRowsPerWg + r_local] = m_run + __log2f(l);
 }
 
 }  // namespace
+
+// fp32 caches too short to be worth a plan and a merge: the key tiles of the
+// longest block a request can reach, walked by one workgroup.
+static bool f32_direct(const fb_attn_shape* sh) {
+    return (long long)sh->max_pages * sh->page_size * sh->head_dim <= kF32DirectWork;
+}
 
 AttnPlanSizes attention_sizes(const fb_pack* pack, const fb_attn_shape* sh,
                               int cu_count) {
@@ -1355,10 +1542,12 @@ AttnPlanSizes attention_sizes(const fb_pack* pack, const fb_attn_shape* sh,
     z.rows_per_unit = pack->bl * g;
     z.row_groups = (z.rows_per_unit + kRowsPerWg - 1) / kRowsPerWg;
     z.unit_cap = pack->tile_cap * sh->Hkv * z.row_groups;
-    // One item per workgroup the chip holds at once (kWgsPerCu per CU): more
-    // splits cost more in partial writes, the merge and per-item start-up
-    // than they win in balance (measured: 8 per CU was 2-25% slower).
-    z.target_items = kWgsPerCu * (cu_count > 0 ? cu_count : 256);
+    // One item per workgroup the chip holds at once (kWgsPerCu per CU in bf16,
+    // kF32WgsPerCu in fp32): more splits cost more in partial writes, the
+    // merge and per-item start-up than they win in balance (measured in bf16:
+    // 8 per CU was 2-25% slower).
+    const bool f32 = sh->dtype == FB_F32;
+    z.target_items = (f32 ? kF32WgsPerCu : kWgsPerCu) * (cu_count > 0 ? cu_count : 256);
     z.item_cap = z.unit_cap + z.target_items;
     z.slot_cap = 2 * z.target_items;
     z.split_cap = z.target_items;   // a split unit holds at least two of the slots
@@ -1373,7 +1562,7 @@ AttnPlanSizes attention_sizes(const fb_pack* pack, const fb_attn_shape* sh,
     z.off_units = take((size_t)z.unit_cap * 2 * sizeof(int32_t));
     z.off_counts = take(4 * sizeof(int32_t));
     z.off_split = take((size_t)z.split_cap * sizeof(int4));
-    if (sh->dtype == FB_BF16) {
+    if (!f32 || !f32_direct(sh)) {
         z.off_part_o = take((size_t)z.slot_cap * kRowsPerWg * D * sizeof(float));
         z.off_part_lse = take((size_t)z.slot_cap * kRowsPerWg * sizeof(float));
     } else {
@@ -1397,14 +1586,19 @@ AttnWs ws_view(void* wsp, const AttnPlanSizes& z) {
 
 }  // namespace
 
-hipError_t launch_attention_plan(const fb_pack* pack, const fb_attn_shape* sh, void* wsp,
-                                 const AttnPlanSizes& z, hipStream_t stream) {
-    if (sh->dtype == FB_F32) return hipSuccess;   // the fp32 path has no plan
+static void launch_plan(const fb_pack* pack, const fb_attn_shape* sh, const AttnWs& ws,
+                        const AttnPlanSizes& z, hipStream_t stream) {
     const int fixed_chunk = sh->kv_split > 0 ? sh->kv_split / kKeyTile : 0;
     const long long max_keys = (long long)sh->max_pages * sh->page_size;
-    hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kPlanThreads), 0, stream, pack_view(pack),
-                       ws_view(wsp, z), sh->Hkv, z.row_groups, z.item_cap, z.slot_cap,
-                       z.split_cap, z.target_items, fixed_chunk, max_keys);
+    hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kPlanThreads), 0, stream, pack_view(pack), ws,
+                       sh->Hkv, z.row_groups, z.item_cap, z.slot_cap, z.split_cap,
+                       z.target_items, fixed_chunk, max_keys);
+}
+
+hipError_t launch_attention_plan(const fb_pack* pack, const fb_attn_shape* sh, void* wsp,
+                                 const AttnPlanSizes& z, hipStream_t stream) {
+    if (sh->dtype == FB_F32) return hipSuccess;   // fp32 plans inside the attention call
+    launch_plan(pack, sh, ws_view(wsp, z), z, stream);
     return hipGetLastError();
 }
 
@@ -1417,25 +1611,39 @@ hipError_t launch_attention(const void* q, const void* k_cache,
     const int g = sh->Hq / sh->Hkv;
     const float scale = sh->sm_scale > 0.f ? sh->sm_scale
                                            : 1.0f / sqrtf((float)sh->head_dim);
-    if (sh->dtype == FB_F32) {
-        hipLaunchKernelGGL(attn_f32_kernel, dim3(pack->tile_cap, sh->Hq),
-                           dim3(kAttnThreads), 0, stream,
-                           static_cast<const float*>(q),
-                           static_cast<const float*>(k_cache),
-                           static_cast<const float*>(v_cache), page_table, pv,
-                           static_cast<float*>(out), sh->Hq, sh->Hkv,
-                           sh->head_dim, pack->bl, sh->page_size, sh->max_pages,
-                           sh->num_pages, scale);
-        return hipGetLastError();
-    }
     const AttnWs ws = ws_view(wsp, z);
     const PlanBounds bounds{pack->B, pack->row_cap, z.unit_cap, z.slot_cap,
                             (long long)sh->max_pages * sh->page_size};
-    hipError_t e = planned ? hipSuccess : launch_attention_plan(pack, sh, wsp, z, stream);
-    if (e != hipSuccess) return e;
     int shift = 0;
     while ((1 << shift) < sh->page_size) ++shift;
     const float scale_log2 = scale * kLog2e;
+    if (sh->dtype == FB_F32) {
+        const bool direct = f32_direct(sh);
+        if (!direct) launch_plan(pack, sh, ws, z, stream);
+        auto launch = [&](auto kernel, int grid) {
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(kAttnThreads), 0, stream,
+                               static_cast<const float*>(q), static_cast<const float*>(k_cache),
+                               static_cast<const float*>(v_cache), page_table, pv, ws,
+                               static_cast<float*>(out), sh->Hq, sh->Hkv, g, pack->bl,
+                               z.row_groups, sh->page_size, shift, sh->max_pages, sh->num_pages,
+                               scale_log2, bounds);
+        };
+        auto of_dim = [&](auto d_c) {
+            constexpr int D = decltype(d_c)::value;
+            if (direct) launch(attn_f32_kernel<D, true>, z.unit_cap);
+            else launch(attn_f32_kernel<D, false>, z.item_cap);
+        };
+        if (sh->head_dim == 32) of_dim(std::integral_constant<int, 32>{});
+        else if (sh->head_dim == 64) of_dim(std::integral_constant<int, 64>{});
+        else of_dim(std::integral_constant<int, 128>{});
+        if (!direct)
+            hipLaunchKernelGGL(combine_kernel<float>, dim3(z.split_cap * kCombineParts),
+                               dim3(kAttnThreads), 0, stream, pv, ws, static_cast<float*>(out),
+                               sh->Hq, sh->Hkv, g, pack->bl, z.row_groups, sh->head_dim, bounds);
+        return hipGetLastError();
+    }
+    hipError_t e = planned ? hipSuccess : launch_attention_plan(pack, sh, wsp, z, stream);
+    if (e != hipSuccess) return e;
     const uint16_t* qb = static_cast<const uint16_t*>(q);
     const uint16_t* kc = static_cast<const uint16_t*>(k_cache);
     const uint16_t* vc = static_cast<const uint16_t*>(v_cache);
