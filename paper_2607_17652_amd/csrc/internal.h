@@ -109,7 +109,9 @@ struct LmSizes {
     int n_vtiles;        // 256-id vocabulary tiles
     int cu;              // compute units the partition count is chosen for
     int grid;            // workgroups: the most any row count needs
-    size_t total;        // workspace bytes (256 partials per workgroup)
+    int few_rows;        // live rows up to which the few-rows form takes the call
+    int few_grid;        // its workgroups, 0 if it is not launched
+    size_t total;        // workspace bytes (256 partials per block)
 };
 LmSizes lm_sizes(const fb_pack* pack, int V, int D, int cu_count);
 hipError_t launch_lmhead(const void* hidden, const void* weight, int D, int V,

@@ -14,7 +14,7 @@
 //                 vocabulary rows wv*128.. and tokens wt*64.. of the tile.
 //                 With Z^T in the accumulators each lane holds one token and
 //                 16 vocabulary ids per MFMA tile, so the per-token reduction
-//                 is mostly in-lane.
+//                 is mostly in-lane.  Up to 128 rows: lm_few_rows.
 // lm_merge_kernel one wave per row: merges the row's partition partials in a
 //                 fixed order into the first partial of the update workspace
 //                 (the rest are set empty), the input of the update kernel.
@@ -40,6 +40,8 @@ constexpr int kRowBytes = kBK * 2;                // 128 B: one row of a stage
 constexpr int kHalfBytes = kTileV * kRowBytes;    // 32 KB: W part of a stage
 constexpr int kStageBytes = 2 * kHalfBytes;       // W part, then H part
 constexpr int kStages = 2;
+constexpr int kFewRows = 128;                     // rows the weight-streaming form takes
+constexpr int kFewStages = 3;
 constexpr int kMergeThreads = 256;
 
 // LDS reads drained, then a workgroup barrier.  The wait is the builtin, not
@@ -91,9 +93,248 @@ __device__ inline int lm_parts_dev(int n_lt, int nv, int cu) {
     return __builtin_amdgcn_readfirstlane((int)(key & 2047));   // uniform: keeps it scalar
 }
 
+// ---- few rows: the weight streamed once -----------------------------------
+// With at most 128 rows the MFMAs of a 256-token tile are mostly padding, so
+// the tile is 64 or 128 tokens wide and the kernel is bound by reading W.  The
+// vocabulary goes to the CUs in equal contiguous ranges of 32-id groups; a
+// wave owns one group of a tile of eight and all tokens, so the W rows it
+// loads are its own, and a wave past the range's end loads and multiplies
+// nothing.  Three 64-wide stages in LDS keep two stages of loads in flight.
+//
+// K is summed as two halves, (first) + (second), and every other workgroup
+// takes the second half first: with every CU at the same K offset the 128-byte
+// pieces read at one time fall on few memory channels where D is a power of
+// two.  The sum of two is the same in either order, so a row of W gives the
+// same logit in any workgroup (equal rows tie exactly).
+//
+// Measured (96 rows, V = 157184, D = 2048: 644 MB of W, 92 us at the read
+// probe's 7.06 TB/s): 180-198 us with the 256-token
+// tile, 112 us here (64 rows: 190 -> 111 us for the whole call; all workgroups
+// starting K together and without the nontemporal hint: 145-150 us).
+__host__ __device__ inline int lm_few_parts(int V, int cu) {
+    const int groups = (V + 31) / 32;
+    return groups < cu ? groups : cu;
+}
+
+__device__ inline void wait_vm_n(bool more, int n_more, int n_less) {
+    // n_more or n_less loads may stay in flight (both among 1, 2, 5, 6)
+    const int n = more ? n_more : n_less;
+    if (n == 1) asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
+    else if (n == 2) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
+    else if (n == 5) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
+    else if (n == 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+    else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+template <int NT>   // 32-token groups: 2 or 4
+__device__ __attribute__((always_inline)) inline void
+lm_few_rows(const uint16_t* __restrict__ H, const uint16_t* __restrict__ W, int D, int V,
+            int row_cap, int cu, const PackView& pv, float4* __restrict__ part,
+            unsigned char* lds) {
+    constexpr int NH = NT / 2;                       // H loads of a wave per stage
+    constexpr int kStage = kHalfBytes + NT * 32 * kRowBytes;
+    const int P = lm_few_parts(V, cu);
+    const int blk = blockIdx.x;
+    if (blk >= P) return;
+    const int groups = (V + 31) / 32;
+    const int g0 = (int)((long long)blk * groups / P);
+    const int g1 = (int)((long long)(blk + 1) * groups / P);
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: so is its group
+    const int lane = tid & 63;
+    const int n = lane & 31;
+    const int h = lane >> 5;
+    const int lrow = lane >> 3;
+
+    // loads: 8 rows of 128 bytes per instruction, chunks swizzled with
+    // (row/2)%8 as in the 256-token form
+    uint32_t w_off[4], h_off[NH];
+    auto chunk = [&](int r) { return (lane & 7) ^ ((r >> 1) & 7); };
+#pragma unroll
+    for (int j = 0; j < NH; ++j) {
+        const int r = (wave * NH + j) * 8 + lrow;
+        h_off[j] = (uint32_t)(((size_t)min(r, row_cap - 1) * D + chunk(r) * 8) * 2);
+    }
+    auto set_group = [&](int grp) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = j * 8 + lrow;
+            const int id = min(grp * 32 + r, V - 1);
+            w_off[j] = (uint32_t)(((size_t)id * D + chunk(r) * 8) * 2);
+        }
+    };
+    const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+    const uint32_t m0_w = __builtin_amdgcn_readfirstlane(lds0 + wave * 4096);
+    const uint32_t m0_h = __builtin_amdgcn_readfirstlane(lds0 + kHalfBytes + wave * NH * 1024);
+
+    const int KS = D / kBK;
+    const int tiles = (g1 - g0 + 7) / 8;
+    const int T = tiles * KS;
+    // K stages in the order taken: from k_start to the end, then from 0
+    const int half = (KS + 1) / 2;
+    const int k_start = (blk & 1) && KS > 1 ? half : 0;
+    const int n_first = (blk & 1) && KS > 1 ? KS - half : half;   // stages before the turn
+    int ld_ks = 0, ld_grp = g0 + wave, ld_slot = 0;   // the next stage to load
+    bool ld_live = ld_grp < g1;
+    set_group(ld_grp);
+    auto issue = [&]() {
+        const uint32_t so = ld_slot * kStage;
+        const int kz = ld_ks + k_start < KS ? ld_ks + k_start : ld_ks + k_start - KS;
+        const uint16_t* wb = W + kz * kBK;
+        const uint16_t* hb = H + kz * kBK;
+        if (ld_live) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)   // read once: nontemporal
+                asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                             :: "s"(m0_w + so + j * 1024), "v"(w_off[j]), "s"(wb) : "memory");
+        }
+#pragma unroll
+        for (int j = 0; j < NH; ++j)
+            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+                         :: "s"(m0_h + so + j * 1024), "v"(h_off[j]), "s"(hb) : "memory");
+        ld_slot = ld_slot == kFewStages - 1 ? 0 : ld_slot + 1;
+        if (++ld_ks == KS) {
+            ld_ks = 0;
+            ld_grp += 8;
+            ld_live = ld_grp < g1;
+            set_group(ld_grp);
+        }
+    };
+
+    const uint32_t swz = (uint32_t)((h ^ ((n >> 1) & 7)) * 16);
+    const uint32_t a_row = (uint32_t)((wave * 32 + n) * kRowBytes);
+    const uint32_t b_row = (uint32_t)(kHalfBytes + n * kRowBytes);
+    floatx16 acc[NT], done[NT];   // the half being summed, the half before it
+    Top top[NT];
+#pragma unroll
+    for (int ti = 0; ti < NT; ++ti) {
+        acc[ti] = done[ti] = floatx16{};
+        top[ti] = top_empty();
+    }
+
+    issue();
+    bool next_live = ld_live;   // whether stage s + 1 holds loads of W for this wave
+    if (T > 1) issue();
+    int s = 0, slot = 0;
+    // One stage: it has landed (stage s + 1 may be in flight), and every wave
+    // is done with stage s - 1, whose slot takes stage s + 2.  The fragments
+    // of K step kk + 1 are read under the MFMAs of kk.
+    auto stage = [&](bool live) __attribute__((always_inline)) {
+        if (s + 1 < T) wait_vm_n(next_live, 4 + NH, NH);
+        else wait_vm0();
+        lds_barrier();
+        if (s + 2 < T) {
+            next_live = ld_live;
+            issue();
+        }
+        if (live) {
+            const unsigned char* st = lds + slot * kStage;
+            bf16x8 a[2], b[2][NT];
+            auto read = [&](int kk) __attribute__((always_inline)) {
+                const uint32_t ko = swz ^ (uint32_t)(kk << 5);
+                a[kk & 1] = *reinterpret_cast<const bf16x8*>(st + a_row + ko);
+#pragma unroll
+                for (int ti = 0; ti < NT; ++ti)
+                    b[kk & 1][ti] = *reinterpret_cast<const bf16x8*>(
+                        st + b_row + ti * 32 * kRowBytes + ko);
+            };
+            read(0);
+#pragma unroll
+            for (int kk = 0; kk < kBK / 16; ++kk) {
+                if (kk + 1 < kBK / 16) read(kk + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int ti = 0; ti < NT; ++ti)
+                    acc[ti] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk & 1], b[kk & 1][ti],
+                                                                      acc[ti], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        slot = slot == kFewStages - 1 ? 0 : slot + 1;
+        ++s;
+    };
+    for (int grp = g0 + wave, tile = 0; tile < tiles; ++tile, grp += 8) {
+        const bool live = grp < g1;
+        for (int ks = 0; ks < n_first; ++ks) stage(live);
+#pragma unroll
+        for (int ti = 0; ti < NT; ++ti) {
+            done[ti] = acc[ti];
+            acc[ti] = floatx16{};
+        }
+        for (int ks = n_first; ks < KS; ++ks) stage(live);
+        if (!live) continue;
+        // lane value r is id grp*32 + (r/4)*8 + h*4 + r%4: increasing in r
+        const int vbase = grp * 32 + h * 4;
+#pragma unroll
+        for (int ti = 0; ti < NT; ++ti) {
+            float f[16];
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                f[r] = vbase + (r >> 2) * 8 + (r & 3) < V ? acc[ti][r] + done[ti][r] : -INFINITY;
+            float vmax = f[0];
+#pragma unroll
+            for (int r = 1; r < 16; ++r) vmax = fmaxf(vmax, f[r]);
+            Top& t = top[ti];
+            if (vmax > t.m) {
+#pragma clang fp contract(off)
+                int r0 = 15;
+#pragma unroll
+                for (int r = 15; r >= 0; --r)
+                    if (f[r] == vmax) r0 = r;
+                const float nmL = scaled_ref(vmax);
+                t.s *= __builtin_amdgcn_exp2f(t.mL - nmL);
+                t.m = vmax;
+                t.mL = nmL;
+                t.idx = vbase + (r0 >> 2) * 8 + (r0 & 3);
+            }
+            if (t.m != -INFINITY) {
+                float e[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    e[r & 3] += __builtin_amdgcn_exp2f(fmaf(f[r], kLog2e, -t.mL));
+                t.s += (e[0] + e[1]) + (e[2] + e[3]);
+            }
+            acc[ti] = floatx16{};
+        }
+    }
+
+    // lane halves, then the eight waves of each token in order
+    __syncthreads();   // the stages' LDS is reused
+    Top* s_w = reinterpret_cast<Top*>(lds);   // [8][NT * 32]
+#pragma unroll
+    for (int ti = 0; ti < NT; ++ti) {
+        Top o;
+        o.m = __shfl_xor(top[ti].m, 32, 64);
+        o.mL = __shfl_xor(top[ti].mL, 32, 64);
+        o.s = __shfl_xor(top[ti].s, 32, 64);
+        o.idx = __shfl_xor(top[ti].idx, 32, 64);
+        const Top t = top_merge(top[ti], o);
+        if (h == 0) s_w[wave * NT * 32 + ti * 32 + n] = t;
+    }
+    __syncthreads();
+    if (tid < NT * 32 && tid < row_cap && pv.row_req[tid] >= 0) {
+        Top t = s_w[tid];
+        for (int w = 1; w < 8; ++w) t = top_merge(t, s_w[w * NT * 32 + tid]);
+        part[(size_t)blk * kTileT + tid] = top_pack(t);
+    }
+}
+
+__global__ void __launch_bounds__(kLmThreads, 1)
+lm_few_kernel(const uint16_t* __restrict__ H, const uint16_t* __restrict__ W, int D, int V,
+              int row_cap, int padded, int cu, int few_rows, PackView pv,
+              float4* __restrict__ part) {
+    __shared__ __attribute__((aligned(16))) unsigned char
+        lds[kFewStages * (kHalfBytes + kFewRows * kRowBytes)];
+    const int n_rows = padded ? row_cap : pv.hdr[kHdrRows];
+    if (n_rows < 1 || n_rows > few_rows) return;   // more rows: lmhead_kernel's
+    if (n_rows > 64) lm_few_rows<4>(H, W, D, V, row_cap, cu, pv, part, lds);
+    else lm_few_rows<2>(H, W, D, V, row_cap, cu, pv, part, lds);
+}
+
 __global__ void __launch_bounds__(kLmThreads, 1)
 lmhead_kernel(const uint16_t* __restrict__ H, const uint16_t* __restrict__ W, int D, int V,
-              int row_cap, int padded, int n_vtiles, int cu, PackView pv,
+              int row_cap, int padded, int n_vtiles, int cu, int few_rows, PackView pv,
               float4* __restrict__ part) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[kStages * kStageBytes];
     __shared__ Top s_top[kTileT];
@@ -104,7 +345,9 @@ lmhead_kernel(const uint16_t* __restrict__ H, const uint16_t* __restrict__ W, in
     // header-count rows; padded rows sit anywhere below row_cap), and the
     // partitions for them; block b is token tile b mod n_lt of partition
     // b / n_lt, and workgroup i takes blocks i, i + gridDim.x, ...
-    const int n_lt = ((padded ? row_cap : pv.hdr[kHdrRows]) + kTileT - 1) / kTileT;
+    const int n_rows = padded ? row_cap : pv.hdr[kHdrRows];
+    if (n_rows <= few_rows) return;   // lm_few_kernel's
+    const int n_lt = (n_rows + kTileT - 1) / kTileT;
     const int P = n_lt > 0 ? lm_parts_dev(n_lt, n_vtiles, cu) : 0;
     for (int blk = blockIdx.x; blk < n_lt * P; blk += gridDim.x) {
     const int rt = blk % n_lt;
@@ -387,13 +630,14 @@ lmhead_kernel(const uint16_t* __restrict__ H, const uint16_t* __restrict__ W, in
 // row's token tile, written by block k * n_lt + tile) merged per lane in
 // increasing k, then across lanes by a fixed butterfly.
 __global__ void __launch_bounds__(kMergeThreads)
-lm_merge_kernel(const float4* __restrict__ lm_part, int n_vtiles, int cu, PackView pv,
-                int row_cap, int padded, float4* __restrict__ upd_part, int nsplit) {
+lm_merge_kernel(const float4* __restrict__ lm_part, int V, int n_vtiles, int cu, int few_rows,
+                PackView pv, int row_cap, int padded, float4* __restrict__ upd_part, int nsplit) {
     const int row = blockIdx.x * (kMergeThreads / 64) + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (row >= row_cap || pv.row_req[row] < 0) return;
-    const int n_lt = ((padded ? row_cap : pv.hdr[kHdrRows]) + kTileT - 1) / kTileT;
-    const int P = lm_parts_dev(n_lt, n_vtiles, cu);
+    const int n_rows = padded ? row_cap : pv.hdr[kHdrRows];
+    const int n_lt = (n_rows + kTileT - 1) / kTileT;
+    const int P = n_rows <= few_rows ? lm_few_parts(V, cu) : lm_parts_dev(n_lt, n_vtiles, cu);
     const size_t base = (size_t)(row / kTileT) * kTileT + row % kTileT;
     const size_t stride = (size_t)n_lt * kTileT;
     Top t = top_empty();
@@ -437,12 +681,22 @@ LmSizes lm_sizes(const fb_pack* pack, int V, int D, int cu_count) {
             memo.emplace(key, grid);
         }
     }
+    // The few-rows form has a block per vocabulary range.  The live rows are
+    // known on the device only, so where the capacity allows more both kernels
+    // are launched and one returns at once.  That costs 2.5 us, so it is done
+    // only where the weight is large (from 256 MB it is 1-2% of the call when
+    // the rows turn out many, against 1.4-1.7x when few) and the capacity at
+    // most 1024 rows, above which so few live ones are unlikely.
+    const bool few = pack->row_cap <= kFewRows ||
+                     (pack->row_cap <= 8 * kFewRows && (long long)V * D >= (1LL << 27));
+    z.few_rows = few ? kFewRows : 0;
+    z.few_grid = few ? lm_few_parts(V, z.cu) : 0;
+    const int blocks = grid > z.few_grid ? grid : z.few_grid;
     // partials: one per block; workgroups: at most eight per CU, each taking
     // blocks in turn (blocks past n_lt * P end at once, but each still holds
     // its CU for a moment)
-    z.total = (size_t)grid * kTileT * sizeof(float4);
+    z.total = (size_t)blocks * kTileT * sizeof(float4);
     z.grid = grid < 8 * z.cu ? grid : 8 * z.cu;
-    (void)D;
     return z;
 }
 
@@ -451,18 +705,23 @@ hipError_t launch_lmhead(const void* hidden, const void* weight, int D, int V,
                          const UpdateSizes& uz, hipStream_t stream) {
     PackView pv = pack_view(pack);
     float4* lm_part = static_cast<float4*>(lm_ws);
-    hipLaunchKernelGGL(lmhead_kernel, dim3((unsigned)z.grid), dim3(kLmThreads), 0, stream,
-                       static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(weight),
-                       D, V, pack->row_cap, pack->layout == FB_PADDED ? 1 : 0, z.n_vtiles, z.cu,
-                       pv, lm_part);
+    const uint16_t* hp = static_cast<const uint16_t*>(hidden);
+    const uint16_t* wp = static_cast<const uint16_t*>(weight);
+    const int padded = pack->layout == FB_PADDED ? 1 : 0;
+    if (z.few_grid > 0)
+        hipLaunchKernelGGL(lm_few_kernel, dim3((unsigned)z.few_grid), dim3(kLmThreads), 0, stream,
+                           hp, wp, D, V, pack->row_cap, padded, z.cu, z.few_rows, pv, lm_part);
+    if (pack->row_cap > kFewRows)
+        hipLaunchKernelGGL(lmhead_kernel, dim3((unsigned)z.grid), dim3(kLmThreads), 0, stream,
+                           hp, wp, D, V, pack->row_cap, padded, z.n_vtiles, z.cu, z.few_rows, pv,
+                           lm_part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int rows_per_wg = kMergeThreads / 64;
     hipLaunchKernelGGL(lm_merge_kernel,
                        dim3((unsigned)((pack->row_cap + rows_per_wg - 1) / rows_per_wg)),
-                       dim3(kMergeThreads), 0, stream, lm_part, z.n_vtiles, z.cu, pv,
-                       pack->row_cap, pack->layout == FB_PADDED ? 1 : 0,
-                       static_cast<float4*>(upd_ws), uz.nsplit);
+                       dim3(kMergeThreads), 0, stream, lm_part, V, z.n_vtiles, z.cu, z.few_rows, pv,
+                       pack->row_cap, padded, static_cast<float4*>(upd_ws), uz.nsplit);
     return hipGetLastError();
 }
 
