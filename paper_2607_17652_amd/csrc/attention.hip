@@ -14,8 +14,9 @@
 //           kv_len; long units are split so the grid has enough items
 //   plan_kernel    one workgroup: counts key tiles, picks the split size,
 //                  emits items (longest first, each with its tile's request
-//                  and first row), per-unit split counts and partial slots,
-//                  and the list of split units
+//                  and first row) with their partial slots, and the list of
+//                  split units; for packs of at most kInlineTiles tiles the
+//                  attention's own waves do this instead (plan_item)
 //   attn_bf16      one workgroup (4 waves x 32 rows) per item: 32-key K and
 //                  V^T tiles streamed through an LDS ring (3 stages at
 //                  D = 128, K refilled a step ahead of V^T; 4 below) by
@@ -55,12 +56,10 @@ constexpr float kRescaleSlack = 8.0f;  // lazy rescale: running max may lag by 2
 // first packed row of its tile (copied here so the attention workgroup's
 // first dependent loads are the item and then the page table).
 enum ItemField { kIUnit = 0, kIKb, kIKe, kISlot, kIB, kIRow0, kIItemInts = 8 };
-enum UnitField { kUSplits = 0, kUSlot0 };
 enum CountField { kCItems = 0, kCUnits, kCChunk, kCSplit };
 
 struct AttnWs {
     int32_t* items;    // [item_cap][kIItemInts]
-    int32_t* units;    // [unit_cap][2]
     int32_t* counts;   // [4]
     int4* split;       // [split_cap]: {unit, pieces, first slot, first row} of the
                        // units with more than one piece
@@ -211,6 +210,29 @@ __device__ inline PlanTile plan_tile(const int32_t* tiles, int t, int n_tiles, l
     return p;
 }
 
+// Split size in key tiles.  With chunk >= total_tiles / target_items the items
+// and the partial slots always fit: a unit of kt key tiles makes
+// ceil(kt/chunk) <= kt/chunk + 1 items, so all units make at most
+// total_tiles/chunk + n_units <= item_cap, and a split unit's
+// ceil(kt/chunk) < 2 kt/chunk slots sum to at most 2 target_items =
+// slot_cap.  A chunk >= kt_max / kMaxSplits keeps every unit within the
+// splits the combine merges.  A requested split size is doubled until
+// both hold.  (Sizes stay below 2^30 key tiles: 32-bit math in the callers.)
+__device__ inline long long split_chunk(long long total_tiles, long long kt_max,
+                                        int target_items, int fixed_chunk_tiles) {
+    const long long up = total_tiles + target_items - 1;
+    long long need = up <= 0xffffffffLL ? (long long)((uint32_t)up / (uint32_t)target_items)
+                                        : up / target_items;
+    const long long need_m = (kt_max + kMaxSplits - 1) / kMaxSplits;
+    if (need_m > need) need = need_m;
+    if (fixed_chunk_tiles > 0) {
+        long long chunk = fixed_chunk_tiles;
+        while (chunk < need) chunk *= 2;
+        return chunk;
+    }
+    return need > kMinChunkTiles ? need : kMinChunkTiles;
+}
+
 __global__ void __launch_bounds__(kPlanThreads)
 plan_kernel(PackView pv, AttnWs ws, int Hkv, int RG, int item_cap, int slot_cap,
             int split_cap, int target_items, int fixed_chunk_tiles, long long max_keys) {
@@ -248,24 +270,7 @@ plan_kernel(PackView pv, AttnWs ws, int Hkv, int RG, int item_cap, int slot_cap,
     const long long total_tiles = red[0] * per_tile;
     const long long kt_max = red[1];
 
-    // Split size.  With chunk >= total_tiles / target_items the items and
-    // the partial slots always fit: a unit of kt key tiles makes
-    // ceil(kt/chunk) <= kt/chunk + 1 items, so all units make at most
-    // total_tiles/chunk + n_units <= item_cap, and a split unit's
-    // ceil(kt/chunk) < 2 kt/chunk slots sum to at most 2 target_items =
-    // slot_cap.  A chunk >= kt_max / kMaxSplits keeps every unit within the
-    // splits the combine merges.  A requested split size is doubled until
-    // both hold.  (Sizes stay below 2^30 key tiles: 32-bit math below.)
-    long long need = (total_tiles + target_items - 1) / target_items;
-    const long long need_m = (kt_max + kMaxSplits - 1) / kMaxSplits;
-    if (need_m > need) need = need_m;
-    long long chunk_ll;
-    if (fixed_chunk_tiles > 0) {
-        chunk_ll = fixed_chunk_tiles;
-        while (chunk_ll < need) chunk_ll *= 2;
-    } else {
-        chunk_ll = need > kMinChunkTiles ? need : kMinChunkTiles;
-    }
+    const long long chunk_ll = split_chunk(total_tiles, kt_max, target_items, fixed_chunk_tiles);
     if (chunk_ll >= (1 << 30)) {
         // beyond any real cache (over 2^30 key tiles per item): nothing is
         // planned and the first tile's request is flagged
@@ -314,7 +319,7 @@ plan_kernel(PackView pv, AttnWs ws, int Hkv, int RG, int item_cap, int slot_cap,
     }
 
     // A round's pieces are staged in LDS, then their items (a piece's
-    // per_tile items are contiguous) and the round's units are written by
+    // per_tile items are contiguous) and the round's split units are written by
     // consecutive threads to consecutive entries, so the stores coalesce;
     // a round with more pieces than the stage holds writes its items from
     // the owning thread instead.
@@ -322,7 +327,7 @@ plan_kernel(PackView pv, AttnWs ws, int Hkv, int RG, int item_cap, int slot_cap,
     __shared__ int4 s_pt[kPlanPieces];   // per piece: tile, splits of the tile, request, first row
     __shared__ int4 s_tl[kPlanThreads];  // per tile of the round: splits, first slot, first
                                          // split entry, first row
-    // the entries a thread writes: unit / item j of every tpi-th tile or
+    // the entries a thread writes: split unit / item j of every tpi-th tile or
     // piece from my_tl on (no division per entry)
     const int tpi = per_tile <= kPlanThreads ? kPlanThreads / per_tile : 1;
     const int my_tl = per_tile <= kPlanThreads ? (int)threadIdx.x / per_tile : 0;
@@ -369,11 +374,9 @@ plan_kernel(PackView pv, AttnWs ws, int Hkv, int RG, int item_cap, int slot_cap,
         __syncthreads();
         int round_tiles = n_tiles - c * kPlanThreads;
         if (round_tiles > kPlanThreads) round_tiles = kPlanThreads;
-        auto write_unit = [&](int tl, int j) {
+        auto write_split = [&](int tl, int j) {
             const int4 q = s_tl[tl];
             const int u = (c * kPlanThreads + tl) * per_tile + j;
-            ws.units[(size_t)u * 2 + kUSplits] = q.x;
-            ws.units[(size_t)u * 2 + kUSlot0] = q.x > 1 ? q.y + j * q.x : -1;
             if (q.x > 1 && q.z + j < split_cap)
                 ws.split[q.z + j] = make_int4(u, q.x, q.y + j * q.x, q.w);
         };
@@ -387,13 +390,13 @@ plan_kernel(PackView pv, AttnWs ws, int Hkv, int RG, int item_cap, int slot_cap,
         };
         if (by_lane) {
             if (my_tl < tpi) {
-                for (int tl = my_tl; tl < round_tiles; tl += tpi) write_unit(tl, my_j);
+                for (int tl = my_tl; tl < round_tiles; tl += tpi) write_split(tl, my_j);
                 if (staged)
                     for (int pc = my_tl; pc < round_pieces; pc += tpi) write_item(pc, my_j);
             }
         } else {
             for (int e = threadIdx.x; e < round_tiles * per_tile; e += kPlanThreads)
-                write_unit(e / per_tile, e % per_tile);
+                write_split(e / per_tile, e % per_tile);
             if (staged)
                 for (int e = threadIdx.x; e < round_pieces * per_tile; e += kPlanThreads)
                     write_item(e / per_tile, e % per_tile);
@@ -409,6 +412,161 @@ plan_kernel(PackView pv, AttnWs ws, int Hkv, int RG, int item_cap, int slot_cap,
         ws.counts[kCChunk] = chunk < (1 << 30) / kKeyTile ? chunk * kKeyTile : -1;   // keys
         ws.counts[kCSplit] = split_before < split_cap ? split_before : split_cap;
     }
+}
+
+// ---- the plan of a small pack, made by the attention's own workgroups ----
+// plan_kernel takes 7-9 us, nearly all of it latency (a launch, dependent
+// reads, barrier rounds), and the attention waits for it.  Up to 64 tiles a
+// wave holds the whole pack, one tile per lane, so every wave of the attention
+// finds its own item with lane moves only: the read of the tile records takes
+// the place of the read of the item record, and no barrier is needed.  Same
+// split size, pieces and partial slots as plan_kernel, so outputs are
+// bit-identical; the order is longest first in four classes (longer than a
+// chunk, a chunk, at least half of one, shorter) instead of by exact length.
+// Each workgroup also stores its item where plan_kernel would (and its split
+// units, which the merge reads), so the workspace then holds this pack's plan
+// as before.  One request's step (3 tiles): 50.8 -> 43.7 us; 8 fp32 requests'
+// attention 86 -> 80.  With four tiles per lane (up to 256 tiles, one wave
+// planning for its workgroup) it gained nothing: several workgroups in turn
+// pay for it on each CU and the coarser order lengthens the tail (24 requests
+// of 3 blocks of 96: 62.3 -> 64.2 us; 64 requests of 4 blocks: 127 -> 129).
+constexpr int kInlineTiles = 64;
+
+struct PlanArgs {
+    int per_tile;          // units of a tile: kv-heads x row groups
+    int tile_cap;
+    int item_cap, split_cap, target_items, fixed_chunk_tiles;
+    long long max_keys;
+};
+
+struct Item {
+    int u, kb, ke, slot, b, row0;
+    int kv_len;            // of the item's tile
+};
+
+// Inclusive scan over the wave's lanes by data-parallel moves (a step costs a
+// few cycles where a shuffle through the LDS path costs about a hundred):
+// within rows of 16, then row ends into the following rows.
+template <typename F>
+__device__ inline int wave_scan(int x, F f) {
+    x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));   // row_shr:1
+    x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));   // row_shr:2
+    x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));   // row_shr:4
+    x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));   // row_shr:8
+    x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));   // row_bcast:15
+    x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));   // row_bcast:31
+    return x;
+}
+
+// The item of workgroup `item`; false past the last one.  Whole waves call it
+// and get the same scalars.
+__device__ inline bool plan_item(const PackView& pv, const AttnWs& ws, const PlanArgs& pa,
+                                 const int item, Item& out) {
+    const int lane = threadIdx.x & 63;
+    // every record of the capacity is read at once with the tile count;
+    // those past the count are dropped below
+    PlanTile p = plan_tile(pv.tiles, lane, pa.tile_cap, pa.max_keys);
+    const int n_tiles = min(pv.hdr[kHdrTiles], pa.tile_cap);
+    if (lane >= n_tiles) p.kt = p.kr = 0;
+    auto scalar = [](int x, int from) { return __builtin_amdgcn_readlane(x, from); };
+    auto add = [](int x, int y) { return x + y; };
+    // (32 bits hold the sum: the host checks the capacities)
+    const long long total = (long long)scalar(wave_scan(p.kt, add), 63) * pa.per_tile;
+    const int kt_max = scalar(wave_scan(p.kt, [](int x, int y) { return max(x, y); }), 63);
+    const long long chunk_ll = split_chunk(total, kt_max, pa.target_items, pa.fixed_chunk_tiles);
+    if (chunk_ll >= (1 << 30)) {
+        if (item == 0 && threadIdx.x == 0) {
+            record_error(pv.hdr, pv.tiles[kTB], FB_DERR_PAGE);
+            ws.counts[kCItems] = ws.counts[kCSplit] = 0;
+        }
+        return false;
+    }
+    const int chunk = (int)chunk_ll;
+    // x / chunk for x < 64 chunks (chunk >= kt_max / kMaxSplits): a float
+    // quotient is at most one off
+    const float rcp = 1.0f / (float)chunk;
+    auto over = [&](int x) {
+        int q = (int)((float)x * rcp);
+        const int r = x - q * chunk;
+        return r < 0 ? q - 1 : r >= chunk ? q + 1 : q;
+    };
+
+    // The tile's pieces by class: `full` of class 1 (a chunk long) and at most
+    // one of another, counted in `cls`.
+    //   cls: class 0 in bits 0-9, class 2 in 10-19, class 3 in 20-29
+    //   in[1]: class 1 in bits 0-15 (at most 64 x 64), split tiles above
+    const int whole_max = (int)(3u * (uint32_t)chunk / 2u);   // a unit up to here stays whole
+    const int ns = p.kt > whole_max ? over(p.kt + chunk - 1) : (p.kt > 0 ? 1 : 0);
+    int full = 0, cls = 0;
+    if (ns > 0) {
+        const bool whole = p.kr <= whole_max;
+        full = whole ? (p.kr == chunk) : min(ns, over(p.kr));
+        if (ns > full) {
+            const int len = whole ? p.kr : p.kr - full * chunk;
+            cls = len > chunk ? 1 : 2 * len >= chunk ? 1 << 10 : 1 << 20;
+        }
+    }
+    const int in[3] = {cls, full + (ns > 1 ? 1 << 16 : 0), ns > 1 ? ns : 0};
+    int at[3], tot[2];   // exclusive prefixes in tile order, totals
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const int inc = wave_scan(in[i], add);
+        at[i] = inc - in[i];
+        if (i < 2) tot[i] = scalar(inc, 63);
+    }
+    const int n0 = tot[0] & 1023, n1 = tot[1] & 0xffff;
+    const int n2 = (tot[0] >> 10) & 1023, n3 = (tot[0] >> 20) & 1023;
+    const int n_items = min((n0 + n1 + n2 + n3) * pa.per_tile, pa.item_cap);
+    if (item == 0) {
+        if (threadIdx.x == 0) {
+            ws.counts[kCItems] = n_items;
+            ws.counts[kCSplit] = min((tot[1] >> 16) * pa.per_tile, pa.split_cap);
+        }
+        // tiles past the page table: reported, not planned
+        if ((int)threadIdx.x < n_tiles && p.kt == 0) record_error(pv.hdr, p.b, FB_DERR_PAGE);
+    }
+    if (item >= n_items) return false;
+    const int piece = item / pa.per_tile;
+    const int j = item - piece * pa.per_tile;
+
+    // the piece's class, its rank in it and the tile that owns it
+    int rank = piece, sh = 0;
+    bool many = false;   // class 1
+    if (rank >= n0) {
+        rank -= n0;
+        many = rank < n1;
+        if (!many) {
+            rank -= n1;
+            sh = 10;
+            if (rank >= n2) {
+                rank -= n2;
+                sh = 20;
+            }
+        }
+    }
+    const int before = many ? at[1] & 0xffff : (at[0] >> sh) & 1023;
+    const int have = many ? full : (cls >> sh) & 1023;
+    const unsigned long long owners = __ballot(rank >= before && rank < before + have);
+    if (owners == 0) return false;   // cannot happen: the ranks cover the items
+    const int t = __ffsll(owners) - 1;
+    const int k = many ? rank - scalar(before, t) : scalar(full, t);
+    const int n = scalar(ns, t);
+    const int slot0 = scalar(at[2], t) * pa.per_tile + j * n;   // the unit's first slot
+    out.kv_len = scalar(p.kv, t);
+    out.b = scalar(p.b, t);
+    out.row0 = scalar(p.row0, t);
+    out.u = t * pa.per_tile + j;
+    out.kb = k * chunk * kKeyTile;
+    out.ke = k == n - 1 ? out.kv_len : min(out.kv_len, out.kb + chunk * kKeyTile);
+    out.slot = n > 1 ? slot0 + k : -1;
+    const int e = (scalar(at[1], t) >> 16) * pa.per_tile + j;   // the unit's entry if split
+    if (threadIdx.x == 0) {
+        int4* it = reinterpret_cast<int4*>(ws.items + (size_t)item * kIItemInts);
+        it[0] = make_int4(out.u, out.kb, out.ke, out.slot);
+        it[1] = make_int4(out.b, out.row0, 0, 0);
+        if (n > 1 && k == 0 && e < pa.split_cap) ws.split[e] = make_int4(out.u, n, slot0, out.row0);
+    }
+    return true;
 }
 
 // --------------------------------------------------------- bf16 MFMA ------
@@ -485,15 +643,17 @@ __device__ inline void wait_vm(int n) {
 }
 
 // FAST: pages hold whole key tiles (page_size >= 32), so a tile's loads share
-// one scalar base; otherwise each lane picks its page.
-template <int D, bool FAST>
+// one scalar base; otherwise each lane picks its page.  INLINE: the
+// workgroups plan for themselves (plan_item) instead of reading plan_kernel's
+// items.
+template <int D, bool FAST, bool INLINE>
 __global__ void __launch_bounds__(kAttnThreads, kWgsPerCu)
 attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_cache,
                  const uint16_t* __restrict__ v_cache,
                  const int32_t* __restrict__ page_table, PackView pv, AttnWs ws,
                  uint16_t* __restrict__ out, int Hq, int Hkv, int g, int bl, int RG,
                  int ps, int ps_shift, int max_pages, int num_pages, float scale_log2,
-                 PlanBounds bounds) {
+                 PlanBounds bounds, PlanArgs pa) {
     using RG_ = Ring<D>;
     constexpr int NS = RG_::kStages;
     __shared__ __attribute__((aligned(16))) unsigned char ring[NS * RG_::kStageBytes];
@@ -507,23 +667,31 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_
     constexpr int NK = RG_::kKCh / kAttnThreads;
     constexpr bool SPLIT_RING = NS == 3 && RG_::kKCh % kAttnThreads == 0;
 
-    // The item's record is read together with the item count (the grid has
-    // item_cap workgroups, so the record is always inside the buffer).
-    const int item = blockIdx.x;
-    const int32_t* it = ws.items + (size_t)item * kIItemInts;
-    const int u = it[kIUnit], kb = it[kIKb], ke = it[kIKe], slot = it[kISlot];
-    const int b = it[kIB], row0 = it[kIRow0];
-    const int n_items = ws.counts[kCItems];
-    // (the empty asm keeps the compiler from sinking the record's loads below
-    // the count check, which would serialize the two round trips)
-    asm volatile("" :: "s"(u), "s"(kb), "s"(ke), "s"(slot), "s"(b), "s"(row0), "s"(n_items));
-    if (item >= n_items) return;
-    if ((unsigned)u >= (unsigned)bounds.unit_cap || kb < 0 || (kb & (kKeyTile - 1)) != 0 ||
-        ke <= kb || (long long)ke > bounds.max_keys || slot < -1 || slot >= bounds.slot_cap ||
-        (unsigned)b >= (unsigned)bounds.n_req || row0 < 0 || row0 > bounds.row_cap - bl) {
-        if (threadIdx.x == 0) record_error(pv.hdr, 0, FB_DERR_PLAN);
-        return;
+    Item w;
+    if constexpr (INLINE) {
+        if (!plan_item(pv, ws, pa, blockIdx.x, w)) return;
+    } else {
+        // The item's record is read together with the item count (the grid has
+        // item_cap workgroups, so the record is always inside the buffer).
+        const int item = blockIdx.x;
+        const int32_t* it = ws.items + (size_t)item * kIItemInts;
+        w.u = it[kIUnit], w.kb = it[kIKb], w.ke = it[kIKe], w.slot = it[kISlot];
+        w.b = it[kIB], w.row0 = it[kIRow0];
+        const int n_items = ws.counts[kCItems];
+        // (the empty asm keeps the compiler from sinking the record's loads below
+        // the count check, which would serialize the two round trips)
+        asm volatile("" :: "s"(w.u), "s"(w.kb), "s"(w.ke), "s"(w.slot), "s"(w.b), "s"(w.row0),
+                     "s"(n_items));
+        if (item >= n_items) return;
+        if ((unsigned)w.u >= (unsigned)bounds.unit_cap || w.kb < 0 ||
+            (w.kb & (kKeyTile - 1)) != 0 || w.ke <= w.kb || (long long)w.ke > bounds.max_keys ||
+            w.slot < -1 || w.slot >= bounds.slot_cap || (unsigned)w.b >= (unsigned)bounds.n_req ||
+            w.row0 < 0 || w.row0 > bounds.row_cap - bl) {
+            if (threadIdx.x == 0) record_error(pv.hdr, 0, FB_DERR_PLAN);
+            return;
+        }
     }
+    const int u = w.u, kb = w.kb, ke = w.ke, slot = w.slot, b = w.b, row0 = w.row0;
     const int rg = u % RG;
     const int c = (u / RG) % Hkv;
     const int32_t* pt = page_table + (size_t)b * max_pages;
@@ -1277,7 +1445,7 @@ combine_kernel(PackView pv, AttnWs ws, T* __restrict__ out, int Hq, int Hkv,
 // element i%4: P never moves between lanes, and V^T is read the same way.
 //
 // DIRECT: one workgroup per unit over all its keys, no plan and no merge (for
-// caches too short to be worth splitting).
+// caches too short to be worth splitting).  INLINE as in the bf16 kernel.
 //
 // Measured (8 requests of 256-2048 prefix keys, 16/4 heads, d = 128: 6.4
 // GFLOP, 42 us at the 154 TFLOP/s of a large fp32 matrix product): the whole
@@ -1301,40 +1469,47 @@ __device__ inline void dma4(const void* src, uint32_t lds_wave_base) {
                  :: "s"(lds_wave_base), "v"(src) : "memory");
 }
 
-template <int D, bool DIRECT>
+template <int D, bool DIRECT, bool INLINE>
 __global__ void __launch_bounds__(kAttnThreads, 2)
 attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k_cache,
                 const float* __restrict__ v_cache, const int32_t* __restrict__ page_table,
                 PackView pv, AttnWs ws, float* __restrict__ out, int Hq, int Hkv, int g, int bl,
                 int RG, int ps, int ps_shift, int max_pages, int num_pages, float scale_log2,
-                PlanBounds bounds) {
+                PlanBounds bounds, PlanArgs pa) {
     using T = F32Tile<D>;
     constexpr int NL = T::kLoads;
     constexpr int DT = D / 32;
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     __shared__ __attribute__((aligned(16))) unsigned char buf[2 * T::kBytes];
 
-    int u, kb = 0, ke, slot = -1;
-    if (DIRECT) {
-        u = blockIdx.x;
-        if (u >= pv.hdr[kHdrTiles] * Hkv * RG) return;
+    Item w;
+    if constexpr (!DIRECT && INLINE) {
+        if (!plan_item(pv, ws, pa, blockIdx.x, w)) return;
     } else {
-        const int32_t* it = ws.items + (size_t)blockIdx.x * kIItemInts;
-        u = it[kIUnit], kb = it[kIKb], ke = it[kIKe], slot = it[kISlot];
-        if ((int)blockIdx.x >= ws.counts[kCItems]) return;
-        if ((unsigned)u >= (unsigned)bounds.unit_cap || kb < 0 || (kb & (kKeyTile - 1)) != 0 ||
-            ke <= kb || (long long)ke > bounds.max_keys || slot < -1 || slot >= bounds.slot_cap) {
-            if (threadIdx.x == 0) record_error(pv.hdr, 0, FB_DERR_PLAN);
-            return;
+        if (DIRECT) {
+            w.u = blockIdx.x;
+            if (w.u >= pv.hdr[kHdrTiles] * Hkv * RG) return;
+        } else {
+            const int32_t* it = ws.items + (size_t)blockIdx.x * kIItemInts;
+            w.u = it[kIUnit], w.kb = it[kIKb], w.ke = it[kIKe], w.slot = it[kISlot];
+            if ((int)blockIdx.x >= ws.counts[kCItems]) return;
+            if ((unsigned)w.u >= (unsigned)bounds.unit_cap || w.kb < 0 ||
+                (w.kb & (kKeyTile - 1)) != 0 || w.ke <= w.kb ||
+                (long long)w.ke > bounds.max_keys || w.slot < -1 || w.slot >= bounds.slot_cap) {
+                if (threadIdx.x == 0) record_error(pv.hdr, 0, FB_DERR_PLAN);
+                return;
+            }
         }
+        const int32_t* tile = pv.tiles + (size_t)(w.u / (RG * Hkv)) * kTileInts;
+        w.b = tile[kTB];
+        w.row0 = tile[kTRow0];
+        w.kv_len = tile[kTKvLen];
+        if (DIRECT) w.kb = 0, w.ke = w.kv_len, w.slot = -1;
     }
+    const int u = w.u, kb = w.kb, ke = w.ke, slot = w.slot, b = w.b, row0 = w.row0;
+    const int kv_len = w.kv_len;
     const int rg = u % RG;
     const int c = (u / RG) % Hkv;
-    const int32_t* tile = pv.tiles + (size_t)(u / (RG * Hkv)) * kTileInts;
-    const int b = tile[kTB];
-    const int row0 = tile[kTRow0];
-    const int kv_len = tile[kTKvLen];
-    if (DIRECT) ke = kv_len;
     const int32_t* pt = page_table + (size_t)b * max_pages;
 
     const int tid = threadIdx.x;
@@ -1559,7 +1734,6 @@ AttnPlanSizes attention_sizes(const fb_pack* pack, const fb_attn_shape* sh,
         return at;
     };
     z.off_items = take((size_t)z.item_cap * kIItemInts * sizeof(int32_t));
-    z.off_units = take((size_t)z.unit_cap * 2 * sizeof(int32_t));
     z.off_counts = take(4 * sizeof(int32_t));
     z.off_split = take((size_t)z.split_cap * sizeof(int4));
     if (!f32 || !f32_direct(sh)) {
@@ -1577,7 +1751,6 @@ namespace {
 AttnWs ws_view(void* wsp, const AttnPlanSizes& z) {
     char* base = static_cast<char*>(wsp);
     return AttnWs{reinterpret_cast<int32_t*>(base + z.off_items),
-                  reinterpret_cast<int32_t*>(base + z.off_units),
                   reinterpret_cast<int32_t*>(base + z.off_counts),
                   reinterpret_cast<int4*>(base + z.off_split),
                   reinterpret_cast<float*>(base + z.off_part_o),
@@ -1617,32 +1790,42 @@ hipError_t launch_attention(const void* q, const void* k_cache,
     int shift = 0;
     while ((1 << shift) < sh->page_size) ++shift;
     const float scale_log2 = scale * kLog2e;
+    // Whether the workgroups plan for themselves: a pack that one wave holds
+    // and whose key tiles 32 bits can sum.
+    const bool inline_plan = !planned && pack->tile_cap <= kInlineTiles &&
+        pack->tile_cap * (bounds.max_keys / kKeyTile + 1) < (1LL << 31);
+    const PlanArgs pa{sh->Hkv * z.row_groups, pack->tile_cap, z.item_cap, z.split_cap,
+                      z.target_items, sh->kv_split > 0 ? sh->kv_split / kKeyTile : 0,
+                      bounds.max_keys};
+    const int combine_grid = (z.split_cap < z.unit_cap ? z.split_cap : z.unit_cap) * kCombineParts;
     if (sh->dtype == FB_F32) {
         const bool direct = f32_direct(sh);
-        if (!direct) launch_plan(pack, sh, ws, z, stream);
+        if (!direct && !inline_plan) launch_plan(pack, sh, ws, z, stream);
         auto launch = [&](auto kernel, int grid) {
             hipLaunchKernelGGL(kernel, dim3(grid), dim3(kAttnThreads), 0, stream,
                                static_cast<const float*>(q), static_cast<const float*>(k_cache),
                                static_cast<const float*>(v_cache), page_table, pv, ws,
                                static_cast<float*>(out), sh->Hq, sh->Hkv, g, pack->bl,
                                z.row_groups, sh->page_size, shift, sh->max_pages, sh->num_pages,
-                               scale_log2, bounds);
+                               scale_log2, bounds, pa);
         };
         auto of_dim = [&](auto d_c) {
             constexpr int D = decltype(d_c)::value;
-            if (direct) launch(attn_f32_kernel<D, true>, z.unit_cap);
-            else launch(attn_f32_kernel<D, false>, z.item_cap);
+            if (direct) launch(attn_f32_kernel<D, true, false>, z.unit_cap);
+            else if (inline_plan) launch(attn_f32_kernel<D, false, true>, z.item_cap);
+            else launch(attn_f32_kernel<D, false, false>, z.item_cap);
         };
         if (sh->head_dim == 32) of_dim(std::integral_constant<int, 32>{});
         else if (sh->head_dim == 64) of_dim(std::integral_constant<int, 64>{});
         else of_dim(std::integral_constant<int, 128>{});
         if (!direct)
-            hipLaunchKernelGGL(combine_kernel<float>, dim3(z.split_cap * kCombineParts),
+            hipLaunchKernelGGL(combine_kernel<float>, dim3(combine_grid),
                                dim3(kAttnThreads), 0, stream, pv, ws, static_cast<float*>(out),
                                sh->Hq, sh->Hkv, g, pack->bl, z.row_groups, sh->head_dim, bounds);
         return hipGetLastError();
     }
-    hipError_t e = planned ? hipSuccess : launch_attention_plan(pack, sh, wsp, z, stream);
+    if (!planned && !inline_plan) launch_plan(pack, sh, ws, z, stream);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const uint16_t* qb = static_cast<const uint16_t*>(q);
     const uint16_t* kc = static_cast<const uint16_t*>(k_cache);
@@ -1652,26 +1835,25 @@ hipError_t launch_attention(const void* q, const void* k_cache,
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(z.item_cap), dim3(kAttnThreads), 0, stream, qb, kc, vc,
                            page_table, pv, ws, ob, sh->Hq, sh->Hkv, g, pack->bl, z.row_groups,
-                           sh->page_size, shift, sh->max_pages, sh->num_pages, scale_log2, bounds);
+                           sh->page_size, shift, sh->max_pages, sh->num_pages, scale_log2, bounds, pa);
     };
-    switch (sh->head_dim) {
-        case 32:
-            if (fast) launch(attn_bf16_kernel<32, true>);
-            else launch(attn_bf16_kernel<32, false>);
-            break;
-        case 64:
-            if (fast) launch(attn_bf16_kernel<64, true>);
-            else launch(attn_bf16_kernel<64, false>);
-            break;
-        default:
-            if (fast) launch(attn_bf16_kernel<128, true>);
-            else launch(attn_bf16_kernel<128, false>);
-            break;
-    }
+    auto of_dim = [&](auto d_c) {
+        constexpr int D = decltype(d_c)::value;
+        if (inline_plan) {
+            if (fast) launch(attn_bf16_kernel<D, true, true>);
+            else launch(attn_bf16_kernel<D, false, true>);
+        } else {
+            if (fast) launch(attn_bf16_kernel<D, true, false>);
+            else launch(attn_bf16_kernel<D, false, false>);
+        }
+    };
+    if (sh->head_dim == 32) of_dim(std::integral_constant<int, 32>{});
+    else if (sh->head_dim == 64) of_dim(std::integral_constant<int, 64>{});
+    else of_dim(std::integral_constant<int, 128>{});
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(combine_kernel<uint16_t>, dim3(z.split_cap * kCombineParts), dim3(kAttnThreads),
-                       0, stream, pv, ws, ob, sh->Hq, sh->Hkv, g, pack->bl,
+    hipLaunchKernelGGL(combine_kernel<uint16_t>, dim3(combine_grid), dim3(kAttnThreads), 0,
+                       stream, pv, ws, ob, sh->Hq, sh->Hkv, g, pack->bl,
                        z.row_groups, sh->head_dim, bounds);
     return hipGetLastError();
 }

@@ -68,7 +68,7 @@ struct AttnPlanSizes {
     int slot_cap;         // split partial slots
     int target_items;     // automatic split target
     int split_cap;        // units with more than one piece (slot_cap / 2)
-    size_t off_items, off_units, off_counts, off_split, off_part_o, off_part_lse, total;
+    size_t off_items, off_counts, off_split, off_part_o, off_part_lse, total;
 };
 AttnPlanSizes attention_sizes(const fb_pack* pack, const fb_attn_shape* sh,
                               int cu_count);
