@@ -720,12 +720,13 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_
     };
 
     // Per-thread chunk geometry, the same for every key tile: byte offset of
-    // the chunk inside its page (K: [slot][d], V^T: [d][slot]) and the key
-    // offset of its first key inside the tile.  Each (load j, wave) is all-K
-    // or all-V, so the global base can be a wave-uniform scalar pair.
+    // the chunk inside its page (K: [slot][d], V^T: [d][slot]) and, where a
+    // tile spans several pages, which of them holds it.  Each (load j, wave)
+    // is all-K or all-V, so the global base can be a wave-uniform scalar pair.
     uint32_t ch_off[NCH];
-    int ch_key[NCH];
+    int ch_page[NCH];
     bool ch_isk[NCH];
+    const int slot_mask = FAST ? kKeyTile - 1 : ps - 1;   // a tile key's slot in its page
 #pragma unroll
     for (int j = 0; j < NCH; ++j) {
         const int s = j * kAttnThreads + tid;
@@ -733,15 +734,15 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_
             const int key = s / CPR;
             const int dchunk = (s % CPR) ^ (key % CPR);
             ch_isk[j] = true;
-            ch_key[j] = key;
-            ch_off[j] = (uint32_t)(key * D + dchunk * 8) * 2u;
+            ch_page[j] = FAST ? 0 : key >> ps_shift;
+            ch_off[j] = (uint32_t)((key & slot_mask) * D + dchunk * 8) * 2u;
         } else {
             const int s2 = s - RG_::kKCh;
             const int d = s2 >> 2;
             const int kc = (s2 & 3) ^ ((d >> 2) & 3);
             ch_isk[j] = false;
-            ch_key[j] = kc * 8;
-            ch_off[j] = (uint32_t)(d * ps + kc * 8) * 2u;
+            ch_page[j] = FAST ? 0 : (kc * 8) >> ps_shift;
+            ch_off[j] = (uint32_t)(d * ps + ((kc * 8) & slot_mask)) * 2u;
         }
     }
     // Which loads fetch K is wave-uniform; make it scalar so the choice of
@@ -777,24 +778,44 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_
     constexpr uint32_t kVdt = 32 * kKeyTile * 2;   // bytes between d tiles of V^T
     auto voff = [&](int dt, int tt) -> uint32_t { return voff0[tt] + dt * kVdt; };
 
+    // Page ids of key tile kt: one where a page holds whole tiles, else those
+    // of its kKeyTile / ps pages (at most four; past the item's last key the
+    // last page again).  They are scalar loads made a step before the tile is
+    // issued, so that their latency is off the path.
+    constexpr int NP = FAST ? 1 : 4;
+    struct Pages {
+        int id[NP];
+    };
+    const int pg_last = (ke - 1) >> ps_shift;
+    auto tile_page = [&](int kt) -> Pages {
+        Pages p;
+        const int first = (kt * kKeyTile) >> ps_shift;
+        p.id[0] = pt[first];
+        if constexpr (!FAST) {
+#pragma unroll
+            for (int i = 1; i < NP; ++i) p.id[i] = pt[min(first + i, pg_last)];
+        }
+        return p;
+    };
+    // a bad page id is read as page 0 and recorded once at the end
+    bool page_err = false;
     // Issue the loads of key tile kt into stage STAGE.
-    // Page id of key tile kt when a page holds whole tiles (ps >= kKeyTile);
-    // loaded one step before the tile is issued so the scalar load's latency
-    // is off the path.
-    auto tile_page = [&](int kt) -> int { return pt[(kt * kKeyTile) >> ps_shift]; };
-    bool page_err = false;   // a bad page id on the whole-tile path (recorded once at the end)
     // PART 0: the tile's K loads, 1: its V^T loads, 2: both
-    auto issue_part = [&](int kt, auto stage_c, int page, auto part_c) __attribute__((always_inline)) {
+    auto issue_part = [&](int kt, auto stage_c, Pages pg, auto part_c) __attribute__((always_inline)) {
         constexpr int STAGE = decltype(stage_c)::value;
         constexpr int PART = decltype(part_c)::value;
         constexpr int J0 = PART == 1 ? NK : 0;
         constexpr int J1 = PART == 0 ? NK : NCH;
         const int key0 = kt * kKeyTile;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const bool okp = (unsigned)pg.id[i] < (unsigned)num_pages;
+            page_err |= !okp;
+            pg.id[i] = okp ? pg.id[i] : 0;
+        }
         if (FAST) {
             // one page per tile: uniform base + per-lane constant offsets
-            const bool okp = (unsigned)page < (unsigned)num_pages;
-            page_err |= !okp;
-            page = okp ? page : 0;
+            const int page = pg.id[0];
             const uint32_t inpage = (uint32_t)(key0 & (ps - 1));
             const size_t poff = (size_t)(uint32_t)page * (size_t)page_bytes;
             const unsigned char* kbase = kb0 + poff + inpage * (uint32_t)(D * 2);
@@ -810,41 +831,26 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_
                              :: "s"(m0), "v"(ch_off[j]), "s"(base) : "memory");
             }
         } else {
-            (void)page;
-            // several pages per tile: per-lane page selection
-            const int pbase = key0 >> ps_shift;
-            const int plast = (ke - 1) >> ps_shift;
-            int pid[4];
-            const int npg = kKeyTile / ps;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                pid[i] = (i < npg && pbase + i <= plast) ? pt[pbase + i] : -1;
+            // several pages per tile: the chunk's own page, picked per lane
+            // (24 requests of 96-wide blocks over pages of 16, d = 64: the
+            // kernel takes 47 us, was 57 with the page ids read when the tile
+            // was issued and the address worked out per lane each time)
 #pragma unroll
             for (int j = J0; j < J1; ++j) {
-                const int kg = key0 + ch_key[j];
-                const int pi = (kg >> ps_shift) - pbase;
-                int page = pid[0];
+                int page = pg.id[0];
 #pragma unroll
-                for (int i = 1; i < 4; ++i) page = pi == i ? pid[i] : page;
-                const bool ok = kg < ke && page >= 0 && page < num_pages;
-                if (kg < ke && !ok) record_error(pv.hdr, b, FB_DERR_PAGE);
-                const unsigned char* src = reinterpret_cast<const unsigned char*>(k_cache);
-                if (ok) {
-                    // ch_off addresses the chunk as if its tile began at slot
-                    // 0 of a page; move it to key kg's slot of its page
-                    const ptrdiff_t shift = (ptrdiff_t)(kg & (ps - 1)) - ch_key[j];
-                    const uint16_t* base =
-                        ch_isk[j] ? k_cache + (size_t)page * page_elems + k_head + shift * D
-                                  : v_cache + (size_t)page * page_elems + v_head + shift;
-                    src = reinterpret_cast<const unsigned char*>(base) + ch_off[j];
-                }
+                for (int i = 1; i < NP; ++i) page = ch_page[j] == i ? pg.id[i] : page;
+                const bool isk = (RG_::kKCh % kAttnThreads == 0) ? (j * kAttnThreads < RG_::kKCh)
+                                                                 : ld_isk[j];
+                const unsigned char* src = (isk ? kb0 : vb0) + ch_off[j] +
+                                           (size_t)(uint32_t)page * (size_t)page_bytes;
                 const uint32_t m0 = m0_base[j] + STAGE * RG_::kStageBytes;
                 asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off"
                              :: "s"(m0), "v"(src) : "memory");
             }
         }
     };
-    auto issue_tile = [&](int kt, auto stage_c, int page) {
+    auto issue_tile = [&](int kt, auto stage_c, const Pages& page) {
         issue_part(kt, stage_c, page, std::integral_constant<int, 2>{});
     };
 
@@ -1021,7 +1027,8 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_
     // Stages in use: i (V), i+1 (K), i+2 .. i+NS-1 in flight.
     static_assert(NS >= 3, "the ring needs the current, next and one loading stage");
     floatx16 s_cur = floatx16{};
-    int pg_next = (!SPLIT_RING && FAST && NS - 1 < nt) ? tile_page(kt0 + NS - 1) : 0;
+    Pages pg_next{};
+    if (!SPLIT_RING && NS - 1 < nt) pg_next = tile_page(kt0 + NS - 1);
     // KIND 0: a step with a refill and the steady-state wait (no runtime
     // checks); 1: a step near the end; 2: the step that brings in the last
     // tile (which may be partial).
@@ -1034,10 +1041,8 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_
             wait_vm((NS - 3) * NCH);
             barrier_raw();
             issue_tile(kt0 + i + NS - 1, std::integral_constant<int, FREE>{}, pg_next);
-            if (FAST) {
-                const int nx = i + NS < nt ? i + NS : nt - 1;   // clamped: no branch
-                pg_next = tile_page(kt0 + nx);
-            }
+            const int nx = i + NS < nt ? i + NS : nt - 1;   // clamped: no branch
+            pg_next = tile_page(kt0 + nx);
         } else {
             int behind = nt - 2 - i;            // tiles issued after tile i+1
             if (behind > NS - 3) behind = NS - 3;
@@ -1045,7 +1050,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_
             barrier_raw();
             if (i + NS - 1 < nt) {
                 issue_tile(kt0 + i + NS - 1, std::integral_constant<int, FREE>{}, pg_next);
-                if (FAST && i + NS < nt) pg_next = tile_page(kt0 + i + NS);
+                if (i + NS < nt) pg_next = tile_page(kt0 + i + NS);
             }
         }
         const unsigned char* kst = ring + NXT * RG_::kStageBytes;
@@ -1072,7 +1077,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_
     // KIND 0: both refills, no runtime checks; 1: a step near the end
     // (K(i+3) may not exist); 2: step nt-2, which takes the last tile's
     // scores and leaves only V^T(nt-1) in flight.
-    int pg_k = 0, pg_v = 0;   // page ids of the next K and V^T tiles to load
+    Pages pg_k{}, pg_v{};   // page ids of the next K and V^T tiles to load
     auto step_split = [&](int i, auto stage_c, auto kind_c) __attribute__((always_inline)) {
         constexpr int STAGE = decltype(stage_c)::value;
         constexpr int KIND = decltype(kind_c)::value;
@@ -1087,11 +1092,9 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_
         if constexpr (KIND != 2) {
             if (KIND == 0 || i + 3 < nt) issue_part(kt0 + i + 3, stage_c, pg_k, KPart{});
             issue_part(kt0 + i + 2, std::integral_constant<int, FREE>{}, pg_v, VPart{});
-            if (FAST) {
-                pg_v = pg_k;
-                const int nx = i + 4 < nt ? i + 4 : nt - 1;   // clamped: no branch
-                pg_k = tile_page(kt0 + nx);
-            }
+            pg_v = pg_k;
+            const int nx = i + 4 < nt ? i + 4 : nt - 1;   // clamped: no branch
+            pg_k = tile_page(kt0 + nx);
         }
         const unsigned char* kst = ring + NXT * RG_::kStageBytes;
         const unsigned char* vst = ring + STAGE * RG_::kStageBytes;
@@ -1111,9 +1114,9 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_
         using C2 = std::integral_constant<int, 2>;
         using KPart = std::integral_constant<int, 0>;
         using VPart = std::integral_constant<int, 1>;
-        const int p0 = FAST ? tile_page(kt0) : 0;
-        const int p1 = (FAST && nt > 1) ? tile_page(kt0 + 1) : 0;
-        const int p2 = (FAST && nt > 2) ? tile_page(kt0 + 2) : 0;
+        const Pages p0 = tile_page(kt0);
+        const Pages p1 = nt > 1 ? tile_page(kt0 + 1) : Pages{};
+        const Pages p2 = nt > 2 ? tile_page(kt0 + 2) : Pages{};
         // K(0), K(1), V^T(0), then Q.  The explicit wait is for K(0) alone
         // (it does not count on Q's loads, which a wave without valid rows
         // skips); Q is waited for where it is used, and as loads complete in
@@ -1128,10 +1131,8 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_
         // the loads "step -1" makes: K(2) and V^T(1)
         if (nt > 2) issue_part(kt0 + 2, C2{}, p2, KPart{});
         if (nt > 1) issue_part(kt0 + 1, C1{}, p1, VPart{});
-        if (FAST) {
-            pg_v = p2;
-            pg_k = nt > 3 ? tile_page(kt0 + 3) : p2;
-        }
+        pg_v = p2;
+        pg_k = nt > 3 ? tile_page(kt0 + 3) : p2;
         if (nt == 1 && valid_last < kKeyTile) mask_tail(s_cur);
         m_run = tile_max(s_cur);
         thr_raw = (m_run + kRescaleSlack) / scale_log2;
@@ -1162,8 +1163,8 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_
     }
     if (nt > 0) {
         if constexpr (!SPLIT_RING) {
-            int pg0[NS - 1];   // page ids of the first tiles, all requested before any load
-            static_for<NS - 1>([&](auto j) { pg0[j] = (FAST && j < nt) ? tile_page(kt0 + j) : 0; });
+            Pages pg0[NS - 1];   // page ids of the first tiles, all requested before any load
+            static_for<NS - 1>([&](auto j) { pg0[j] = j < nt ? tile_page(kt0 + j) : Pages{}; });
             static_for<NS - 1>([&](auto j) {
                 if (j < nt) issue_tile(kt0 + j, j, pg0[j]);
             });
