@@ -645,8 +645,9 @@ __device__ inline void wait_vm(int n) {
 // FAST: pages hold whole key tiles (page_size >= 32), so a tile's loads share
 // one scalar base; otherwise each lane picks its page.  INLINE: the
 // workgroups plan for themselves (plan_item) instead of reading plan_kernel's
-// items.
-template <int D, bool FAST, bool INLINE>
+// items.  FULL: every wave of a workgroup has query rows (a unit's rows come in
+// whole 128s); a template, as the test in each step costs the full shapes 1-2%.
+template <int D, bool FAST, bool INLINE, bool FULL>
 __global__ void __launch_bounds__(kAttnThreads, kWgsPerCu)
 attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_cache,
                  const uint16_t* __restrict__ v_cache,
@@ -703,7 +704,11 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_
     const int h = lane >> 5;
     const int r_local = wave * 32 + n;
     const int r = rg * kRowsPerWg + r_local;
-    const bool row_ok = r < bl * g;
+    const bool row_ok = FULL || r < bl * g;
+    // A wave without query rows only loads: its MFMAs and exps would take issue
+    // slots from the waves that have some (64 requests, d = 128, 32 rows per
+    // unit: 214 -> 172 us; d = 64, 8 rows: 122 -> 85).
+    const bool wave_ok = FULL || __builtin_amdgcn_readfirstlane(rg * kRowsPerWg + wave * 32) < bl * g;
     const int pos_local = row_ok ? r / g : 0;
     const int hg = row_ok ? r % g : 0;
     const size_t q_off = ((size_t)(row0 + pos_local) * Hq + c * g + hg) * D;
@@ -1056,6 +1061,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_
         const unsigned char* kst = ring + NXT * RG_::kStageBytes;
         const unsigned char* vst = ring + STAGE * RG_::kStageBytes;   // V^T offsets include the K part
 
+        if (!wave_ok) return;
         floatx16 s_nxt = floatx16{};
         phase1(kst, s_cur, s_nxt);
         if constexpr (KIND == 2) {
@@ -1098,6 +1104,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_
         }
         const unsigned char* kst = ring + NXT * RG_::kStageBytes;
         const unsigned char* vst = ring + STAGE * RG_::kStageBytes;
+        if (!wave_ok) return;
         floatx16 s_nxt = floatx16{};
         phase1(kst, s_cur, s_nxt);
         if constexpr (KIND == 2) {
@@ -1247,6 +1254,7 @@ attn_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k_
             }
         }
     } else {
+        if (!row_ok) return;   // the merge reads valid rows only
         float* po = ws.part_o + ((size_t)slot * kRowsPerWg + r_local) * D;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) {
@@ -1840,13 +1848,16 @@ hipError_t launch_attention(const void* q, const void* k_cache,
     };
     auto of_dim = [&](auto d_c) {
         constexpr int D = decltype(d_c)::value;
-        if (inline_plan) {
-            if (fast) launch(attn_bf16_kernel<D, true, true>);
-            else launch(attn_bf16_kernel<D, false, true>);
-        } else {
-            if (fast) launch(attn_bf16_kernel<D, true, false>);
-            else launch(attn_bf16_kernel<D, false, false>);
-        }
+        auto of_plan = [&](auto inline_c, auto full_c) {
+            constexpr bool I = decltype(inline_c)::value, F = decltype(full_c)::value;
+            if (fast) launch(attn_bf16_kernel<D, true, I, F>);
+            else launch(attn_bf16_kernel<D, false, I, F>);
+        };
+        const bool full = z.rows_per_unit % kRowsPerWg == 0;
+        if (inline_plan && full) of_plan(std::true_type{}, std::true_type{});
+        else if (inline_plan) of_plan(std::true_type{}, std::false_type{});
+        else if (full) of_plan(std::false_type{}, std::true_type{});
+        else of_plan(std::false_type{}, std::false_type{});
     };
     if (sh->head_dim == 32) of_dim(std::integral_constant<int, 32>{});
     else if (sh->head_dim == 64) of_dim(std::integral_constant<int, 64>{});
