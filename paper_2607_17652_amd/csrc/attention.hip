@@ -1284,25 +1284,32 @@ __device__ inline void store_out4<float>(float* p, const float4& v) {
     *reinterpret_cast<float4*>(p) = v;
 }
 
-// Each split unit's rows are merged by kCombineParts workgroups of
-// kCombineRows rows (workgroup b takes entry b / kCombineParts of the plan's
-// list of split units, so the grid covers only units that can be split): a row's per-split log-sum-exp weights go to LDS once,
-// then every thread merges 16-byte columns of its rows, up to eight splits'
-// loads in flight at a time.
-constexpr int kCombineRows = 32;
-constexpr int kCombineParts = kRowsPerWg / kCombineRows;
-
-template <typename T>
+// Each split unit's rows are merged by kRowsPerWg / R workgroups of R rows
+// (workgroup b takes entry b / parts of the plan's list of split units, so the
+// grid covers only units that can be split): a row's per-split log-sum-exp
+// weights go to LDS once, then every thread merges 16-byte columns of its
+// rows, up to IF splits' loads in flight at a time.
+//
+// With few units it is bound by the trips to memory that follow one another,
+// so a workgroup takes few rows (one column group per thread); with many, by
+// the workgroups launched (most find no split unit).  Kernel trace, R = 32 / 16
+// / 8: 12 units in nine pieces 8.6 / 6.3 / 5.5 us; 128 (fp32) 9.1 / 8.5 / 10.9;
+// 256 15.1 / 14.4 / 19.2; 576 with few split 6.6 / 7.3 / 15.0; 768 5.2 / 5.2 / 8.9.
+template <typename T, int R, int IF>
 __global__ void __launch_bounds__(kAttnThreads)
 combine_kernel(PackView pv, AttnWs ws, T* __restrict__ out, int Hq, int Hkv,
                int g, int bl, int RG, int D, PlanBounds bounds) {
-    __shared__ float wgt[kMaxSplits][kCombineRows];
-    __shared__ float inv_den[kCombineRows];
-    const int su = blockIdx.x / kCombineParts;
-    const int part = blockIdx.x % kCombineParts;
-    if (su >= ws.counts[kCSplit]) return;
-    // the plan's record of this split unit: no further lookups before the loads
+    constexpr int kParts = kRowsPerWg / R;
+    __shared__ float wgt[kMaxSplits][R];
+    __shared__ float inv_den[R];
+    const int su = blockIdx.x / kParts;
+    const int part = blockIdx.x % kParts;
+    // the plan's record of this split unit (no further lookups before the
+    // loads), read together with the count: the grid stays inside the list
     const int4 rec = ws.split[su];
+    const int n_split = ws.counts[kCSplit];
+    asm volatile("" :: "s"(rec.x), "s"(rec.y), "s"(rec.z), "s"(rec.w), "s"(n_split));
+    if (su >= n_split) return;
     const int u = rec.x;
     const int ns = rec.y;   // 2 .. kMaxSplits (plan)
     if (ns <= 1) return;
@@ -1315,8 +1322,8 @@ combine_kernel(PackView pv, AttnWs ws, T* __restrict__ out, int Hq, int Hkv,
     }
     const int rg = u % RG;
     const int c = (u / RG) % Hkv;
-    const int rbase = part * kCombineRows;
-    const int nrows = min(kCombineRows, bl * g - rg * kRowsPerWg - rbase);
+    const int rbase = part * R;
+    const int nrows = min(R, bl * g - rg * kRowsPerWg - rbase);
     if (nrows <= 0) return;
     const int per_row = D / 4;
     const int n_el = nrows * per_row;
@@ -1375,7 +1382,7 @@ combine_kernel(PackView pv, AttnWs ws, T* __restrict__ out, int Hq, int Hkv,
     // the thread's column groups (at most kMaxGroups) is issued before the
     // weights are computed, so the workgroup waits for one round trip.
     constexpr int kFastSplits = 4;
-    constexpr int kMaxGroups = kCombineRows * kMaxHeadDim / 4 / kAttnThreads;
+    constexpr int kMaxGroups = (R * kMaxHeadDim / 4 + kAttnThreads - 1) / kAttnThreads;
     const int n_grp = (n_el + kAttnThreads - 1) / kAttnThreads;   // workgroup-uniform
     if (ns <= kFastSplits && n_grp <= kMaxGroups) {
         f32x4 v[kMaxGroups][kFastSplits];
@@ -1403,9 +1410,9 @@ combine_kernel(PackView pv, AttnWs ws, T* __restrict__ out, int Hq, int Hkv,
         }
         return;
     }
-    // More splits: a thread's first column group has its loads (up to eight)
-    // issued before the weights are ready; then eight at a time per group.
-    constexpr int kInFlight = 8;
+    // More splits: a thread's first column group has its loads (up to IF)
+    // issued before the weights are ready; then IF at a time per group.
+    constexpr int kInFlight = IF;
     f32x4 first[kInFlight];
     {
         const float* src = src_of(min((int)threadIdx.x, n_el - 1));
@@ -1806,7 +1813,19 @@ hipError_t launch_attention(const void* q, const void* k_cache,
     const PlanArgs pa{sh->Hkv * z.row_groups, pack->tile_cap, z.item_cap, z.split_cap,
                       z.target_items, sh->kv_split > 0 ? sh->kv_split / kKeyTile : 0,
                       bounds.max_keys};
-    const int combine_grid = (z.split_cap < z.unit_cap ? z.split_cap : z.unit_cap) * kCombineParts;
+    auto combine = [&](auto elt) {
+        using T = decltype(elt);
+        const int units = z.split_cap < z.unit_cap ? z.split_cap : z.unit_cap;
+        auto go = [&](auto kernel, int rows) {
+            hipLaunchKernelGGL(kernel, dim3(units * (kRowsPerWg / rows)), dim3(kAttnThreads), 0,
+                               stream, pv, ws, static_cast<T*>(out), sh->Hq, sh->Hkv, g, pack->bl,
+                               z.row_groups, sh->head_dim, bounds);
+        };
+        // the lines lie between the sizes measured at combine_kernel
+        if (units <= 64) go(combine_kernel<T, 8, 16>, 8);
+        else if (units <= 256) go(combine_kernel<T, 16, 8>, 16);
+        else go(combine_kernel<T, 32, 8>, 32);
+    };
     if (sh->dtype == FB_F32) {
         const bool direct = f32_direct(sh);
         if (!direct && !inline_plan) launch_plan(pack, sh, ws, z, stream);
@@ -1827,10 +1846,7 @@ hipError_t launch_attention(const void* q, const void* k_cache,
         if (sh->head_dim == 32) of_dim(std::integral_constant<int, 32>{});
         else if (sh->head_dim == 64) of_dim(std::integral_constant<int, 64>{});
         else of_dim(std::integral_constant<int, 128>{});
-        if (!direct)
-            hipLaunchKernelGGL(combine_kernel<float>, dim3(combine_grid),
-                               dim3(kAttnThreads), 0, stream, pv, ws, static_cast<float*>(out),
-                               sh->Hq, sh->Hkv, g, pack->bl, z.row_groups, sh->head_dim, bounds);
+        if (!direct) combine(float());
         return hipGetLastError();
     }
     if (!planned && !inline_plan) launch_plan(pack, sh, ws, z, stream);
@@ -1864,9 +1880,7 @@ hipError_t launch_attention(const void* q, const void* k_cache,
     else of_dim(std::integral_constant<int, 128>{});
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(combine_kernel<uint16_t>, dim3(combine_grid), dim3(kAttnThreads), 0,
-                       stream, pv, ws, ob, sh->Hq, sh->Hkv, g, pack->bl,
-                       z.row_groups, sh->head_dim, bounds);
+    combine(uint16_t());
     return hipGetLastError();
 }
 

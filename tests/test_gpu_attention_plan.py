@@ -110,3 +110,30 @@ def test_inline_plan_reports_blocks_past_the_page_table():
         out.append((step.out.clone(), s["code"], s["request"]))
     assert out[0][1] == out[1][1] == fb.FB_DERR_PAGE and out[0][2] == out[1][2]
     assert torch.equal(out[0][0], out[1][0])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,W,Hkv", [(4, 2, 8), (13, 5, 1), (16, 4, 4), (13, 5, 4)])
+def test_merge_of_every_row_split(dtype, B, W, Hkv):
+    """64, 65, 256 and 260 units (the edges of the merge's row counts), each in
+    many pieces, against the same units in one piece: float32 sums in another
+    order, and bf16 outputs rounded once (a weight's rounding to bf16 differs
+    with the running maximum)."""
+    wl = synth.workload("single", dtype=dtype, B=B, Hq=8, Hkv=Hkv, d=64, bl=16, page_size=32,
+                        W_max=W, window=("fixed", W), prefix=("uniform", 600, 1500), n_blocks=8)
+    host = synth.make_host_state(wl, seed=2)
+    t = synth.make_device_tensors(wl, host, 2, device="cuda", with_logits=False)
+    log(f"[plan] merge {dtype} B={B} W={W} Hkv={Hkv}")
+    outs = []
+    for split in (64, 1 << 14):
+        step = WavefrontStep(wl, host, dict(t, logits=None), kv_split=split)
+        step.pack_step()
+        step.kv_step()
+        step.attention_step()
+        torch.cuda.synchronize()
+        assert fb.fb_pack_read_status(step.pack)["code"] == 0
+        outs.append(step.out.double())
+    err = (outs[0] - outs[1]).norm() / outs[1].norm()
+    # bf16: each of about 1000 weights is rounded by at most 2^-9, independently,
+    # and the output by 2^-9; float32: a few 2^-24
+    assert float(err) < (2 ** -8 if dtype == "bf16" else 1e-6)
