@@ -1,0 +1,73 @@
+"""The window prologue where its loads change form: fewer pair groups than
+threads, a last round that is partly filled, several rounds, a head group that
+is no power of two, one-position blocks, and inputs beyond the size from which
+they are read with the streaming hint.  Every live row against the rotation in
+float64; values and positions outside the windows exactly."""
+import numpy as np
+import pytest
+import torch
+
+from harness import log
+from paper_2607_17652_amd import binding as fb
+from paper_2607_17652_amd import synth
+from paper_2607_17652_amd.runner import WavefrontStep
+
+pytestmark = pytest.mark.gpu
+
+
+def _rotate(x, pos, base):
+    """x [n, H, d] float64, pos [n]."""
+    d = x.shape[-1]
+    ang = pos.double()[:, None] * base ** (-2.0 * torch.arange(d // 2, device="cuda").double() / d)
+    c, s = torch.cos(ang)[:, None], torch.sin(ang)[:, None]
+    lo, hi = x[..., : d // 2], x[..., d // 2:]
+    mag = torch.sqrt(lo ** 2 + hi ** 2)
+    return torch.cat([lo * c - hi * s, hi * c + lo * s], -1), torch.cat([mag, mag], -1)
+
+
+def _close(got, x, pos, dtype):
+    ref, mag = _rotate(x.double(), pos, 10000.0)
+    # the rounding to the dtype, and float32 products with rounded cos and sin
+    rel = 2.0 ** -8 if dtype == "bf16" else 2.0 ** -23
+    assert torch.all((got.double() - ref).abs() <= rel * ref.abs() + 8 * 2.0 ** -24 * mag + 1e-30)
+
+
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,d,bl,W", [
+    ("bf16", 3, 1, 1, 32, 1, 2),        # 2 pair groups
+    ("bf16", 2, 6, 2, 64, 8, 3),        # groups of 3 heads, 96 pair groups
+    ("f32", 2, 6, 2, 64, 16, 3),        # one and a half rounds of fp32
+    ("bf16", 2, 9, 1, 128, 32, 2),      # two and a quarter rounds
+    ("f32", 2, 8, 8, 128, 33, 2),       # odd block length: values one by one
+    ("bf16", 2, 16, 2, 128, 128, 2),    # eight rounds, two of keys
+    ("f32", 256, 32, 8, 128, 16, 4),    # 403 MB of inputs: streaming loads
+    ("bf16", 256, 32, 8, 128, 32, 4),   # 403 MB
+])
+def test_prologue_forms(dtype, B, Hq, Hkv, d, bl, W):
+    log(f"[prologue] {dtype} B={B} Hq={Hq} Hkv={Hkv} d={d} bl={bl}")
+    wl = synth.workload("single", dtype=dtype, B=B, Hq=Hq, Hkv=Hkv, d=d, bl=bl, page_size=32,
+                        W_max=W, window=("uniform", 1, W), prefix=("uniform", bl, 8 * bl + 64),
+                        n_blocks=max(4, W))
+    host = synth.make_host_state(wl, seed=21)
+    t = synth.make_device_tensors(wl, host, 21, device="cuda", with_logits=False)
+    step = WavefrontStep(wl, host, dict(t, logits=None))
+    step.pack_step()
+    q_out = torch.full_like(t["q"], 3.0)
+    k0, v0 = t["k_cache"].clone(), t["v_cache"].clone()
+    fb.fb_window_prologue(t["q"], q_out, t["k_new"], t["v_new"], t["k_cache"], t["v_cache"],
+                          step.page_table, step.pack, step.shape)
+    torch.cuda.synchronize()
+    assert fb.fb_pack_read_status(step.pack)["code"] == 0
+    view = step.pack.view()
+    live = torch.nonzero(view["row_req"] >= 0).flatten()
+    pos, req = view["row_pos"][live].long(), view["row_req"][live].long()
+    dead = torch.nonzero(view["row_req"] < 0).flatten()
+    assert torch.all(q_out[dead] == 3.0)
+    page = step.page_table[req, pos // 32].long()
+    for part in torch.arange(len(live), device="cuda").split(4096):
+        r, p, g = live[part], pos[part], page[part]
+        _close(q_out[r], t["q"][r], p, dtype)
+        _close(t["k_cache"][g, :, p % 32], t["k_new"][r], p, dtype)
+        assert torch.equal(t["v_cache"][g, :, :, p % 32], t["v_new"][r])
+    t["k_cache"][page, :, pos % 32] = k0[page, :, pos % 32]
+    t["v_cache"][page, :, :, pos % 32] = v0[page, :, :, pos % 32]
+    assert torch.equal(t["k_cache"], k0) and torch.equal(t["v_cache"], v0)
