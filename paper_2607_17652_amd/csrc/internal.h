@@ -110,7 +110,7 @@ struct LmSizes {
     int cu;              // compute units the partition count is chosen for
     int grid;            // workgroups: the most any row count needs
     int few_rows;        // live rows up to which the few-rows form takes the call
-    int few_grid;        // its workgroups, 0 if it is not launched
+    int few_grid;        // its workgroups, 0 if it is not used
     size_t total;        // workspace bytes (256 partials per block)
 };
 LmSizes lm_sizes(const fb_pack* pack, int V, int D, int cu_count);

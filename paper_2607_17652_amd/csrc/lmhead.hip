@@ -322,21 +322,28 @@ lm_few_rows(const uint16_t* __restrict__ H, const uint16_t* __restrict__ W, int 
 
 __global__ void __launch_bounds__(kLmThreads, 1)
 lm_few_kernel(const uint16_t* __restrict__ H, const uint16_t* __restrict__ W, int D, int V,
-              int row_cap, int padded, int cu, int few_rows, PackView pv,
-              float4* __restrict__ part) {
+              int row_cap, int padded, int cu, PackView pv, float4* __restrict__ part) {
     __shared__ __attribute__((aligned(16))) unsigned char
         lds[kFewStages * (kHalfBytes + kFewRows * kRowBytes)];
     const int n_rows = padded ? row_cap : pv.hdr[kHdrRows];
-    if (n_rows < 1 || n_rows > few_rows) return;   // more rows: lmhead_kernel's
+    if (n_rows < 1 || n_rows > kFewRows) return;
     if (n_rows > 64) lm_few_rows<4>(H, W, D, V, row_cap, cu, pv, part, lds);
     else lm_few_rows<2>(H, W, D, V, row_cap, cu, pv, part, lds);
 }
 
+// FEW: calls of at most few_rows live rows, which only the device knows, take
+// the few-rows form here (a launch of its own that returns at once when they
+// are more cost 2 us).  An instance of its own, as the argument and the test
+// alone cost the large calls 2% (20416 rows, V = 157184, D = 2048: 11.21 ->
+// 11.45 ms).
+template <bool FEW>
 __global__ void __launch_bounds__(kLmThreads, 1)
 lmhead_kernel(const uint16_t* __restrict__ H, const uint16_t* __restrict__ W, int D, int V,
               int row_cap, int padded, int n_vtiles, int cu, int few_rows, PackView pv,
               float4* __restrict__ part) {
-    __shared__ __attribute__((aligned(16))) unsigned char lds[kStages * kStageBytes];
+    constexpr int kFewLds = kFewStages * (kHalfBytes + kFewRows * kRowBytes);
+    __shared__ __attribute__((aligned(16))) unsigned char
+        lds[FEW && kFewLds > kStages * kStageBytes ? kFewLds : kStages * kStageBytes];
     __shared__ Top s_top[kTileT];
     __shared__ int s_live;
 
@@ -346,7 +353,11 @@ lmhead_kernel(const uint16_t* __restrict__ H, const uint16_t* __restrict__ W, in
     // partitions for them; block b is token tile b mod n_lt of partition
     // b / n_lt, and workgroup i takes blocks i, i + gridDim.x, ...
     const int n_rows = padded ? row_cap : pv.hdr[kHdrRows];
-    if (n_rows <= few_rows) return;   // lm_few_kernel's
+    if (FEW && n_rows <= few_rows) {
+        if (n_rows > 64) lm_few_rows<4>(H, W, D, V, row_cap, cu, pv, part, lds);
+        else if (n_rows > 0) lm_few_rows<2>(H, W, D, V, row_cap, cu, pv, part, lds);
+        return;
+    }
     const int n_lt = (n_rows + kTileT - 1) / kTileT;
     const int P = n_lt > 0 ? lm_parts_dev(n_lt, n_vtiles, cu) : 0;
     for (int blk = blockIdx.x; blk < n_lt * P; blk += gridDim.x) {
@@ -682,11 +693,10 @@ LmSizes lm_sizes(const fb_pack* pack, int V, int D, int cu_count) {
         }
     }
     // The few-rows form has a block per vocabulary range.  The live rows are
-    // known on the device only, so where the capacity allows more both kernels
-    // are launched and one returns at once.  That costs 2.5 us, so it is done
-    // only where the weight is large (from 256 MB it is 1-2% of the call when
-    // the rows turn out many, against 1.4-1.7x when few) and the capacity at
-    // most 1024 rows, above which so few live ones are unlikely.
+    // known on the device only; where the capacity allows more, the kernel
+    // chooses by them, if the weight is large (from 256 MB the few-rows form is
+    // 1.4-1.7x as fast where it applies) and the capacity at most 1024 rows,
+    // above which so few live ones are unlikely.
     const bool few = pack->row_cap <= kFewRows ||
                      (pack->row_cap <= 8 * kFewRows && (long long)V * D >= (1LL << 27));
     z.few_rows = few ? kFewRows : 0;
@@ -708,13 +718,17 @@ hipError_t launch_lmhead(const void* hidden, const void* weight, int D, int V,
     const uint16_t* hp = static_cast<const uint16_t*>(hidden);
     const uint16_t* wp = static_cast<const uint16_t*>(weight);
     const int padded = pack->layout == FB_PADDED ? 1 : 0;
-    if (z.few_grid > 0)
+    auto tiles = [&](auto kernel, int wgs) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)wgs), dim3(kLmThreads), 0, stream, hp, wp, D, V,
+                           pack->row_cap, padded, z.n_vtiles, z.cu, z.few_rows, pv, lm_part);
+    };
+    if (pack->row_cap <= kFewRows)
         hipLaunchKernelGGL(lm_few_kernel, dim3((unsigned)z.few_grid), dim3(kLmThreads), 0, stream,
-                           hp, wp, D, V, pack->row_cap, padded, z.cu, z.few_rows, pv, lm_part);
-    if (pack->row_cap > kFewRows)
-        hipLaunchKernelGGL(lmhead_kernel, dim3((unsigned)z.grid), dim3(kLmThreads), 0, stream,
-                           hp, wp, D, V, pack->row_cap, padded, z.n_vtiles, z.cu, z.few_rows, pv,
-                           lm_part);
+                           hp, wp, D, V, pack->row_cap, padded, z.cu, pv, lm_part);
+    else if (z.few_grid > 0)
+        tiles(lmhead_kernel<true>, z.grid > z.few_grid ? z.grid : z.few_grid);
+    else
+        tiles(lmhead_kernel<false>, z.grid);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int rows_per_wg = kMergeThreads / 64;

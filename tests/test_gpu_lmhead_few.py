@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
     (157184, 1024, dict(bl=32, W_max=4, window=("fixed", 4))),          # 128: the form's last
     (40000, 256, dict(bl=43, W_max=3, window=("fixed", 3))),            # 129: past it
     (65537, 2048, dict(B=4, bl=32, W_max=4, window=("fixed", 1))),      # 128 live of 512
-    (65537, 2048, dict(B=5, bl=32, W_max=4, window=("fixed", 1))),      # 160: both launched
+    (65537, 2048, dict(B=5, bl=32, W_max=4, window=("fixed", 1))),      # 160: past the form
     (9001, 256, dict(B=4, bl=8, W_max=4, window=("uniform", 1, 4), layout="padded")),
 ])
 def test_lmhead_few_rows(V, D, kw):
