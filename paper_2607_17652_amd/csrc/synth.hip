@@ -123,9 +123,10 @@ __device__ inline uint16_t level_value<uint16_t>(float a) {
     return (uint16_t)(__float_as_uint(a) >> 16);   // exact: checked on the host
 }
 
-// One workgroup per (row, vocabulary split).  Vector path: rows start on a
-// 16-byte boundary (V * sizeof(T) % 16 == 0), 16-byte stores; else one
-// element per store.
+// One workgroup per (row, vocabulary split), bound by the writes: each split
+// stores its part of the row's 16-byte-aligned body whole, wherever the row
+// starts; the first and last split also store the few elements around the
+// body.
 template <typename T>
 __global__ void __launch_bounds__(kFillThreads)
 synth_fill_kernel(const int2* __restrict__ pred, PackView pv, int V, int nsplit, int chunk,
@@ -137,29 +138,29 @@ synth_fill_kernel(const int2* __restrict__ pred, PackView pv, int V, int nsplit,
     const int l = pr.y & 3;
     const float lf = l == 0 ? levels.x : l == 1 ? levels.y : l == 2 ? levels.z : levels.w;
     const T a = level_value<T>(lf);
-    const int v0 = k * chunk;
-    const int v1 = min(V, v0 + chunk);
     T* z = logits + (size_t)row * V;
     constexpr int E = 16 / sizeof(T);
-    if (((size_t)V * sizeof(T)) % 16 == 0) {
-        // chunk is a multiple of 8 elements, so v0 is 16-byte aligned
-        // v1 - v0 is a multiple of E here (chunk % 8 == 0 and V % E == 0)
-        const uint32_t abits = sizeof(T) == 2 ? (uint32_t)(uint16_t)a : __float_as_uint((float)a);
-        for (int v = v0 + threadIdx.x * E; v < v1; v += kFillThreads * E) {
-            uint32_t wd[4] = {0u, 0u, 0u, 0u};
-            const int off = pr.x - v;                       // in [0, E) if k is here
-            if (off >= 0 && off < E) {
-                const int word = sizeof(T) == 2 ? off >> 1 : off;
-                const uint32_t val = sizeof(T) == 2 ? abits << ((off & 1) * 16) : abits;
+    const int head = min(V, (int)((16 - ((uintptr_t)z & 15)) & 15) / (int)sizeof(T));
+    const int body_end = head + (V - head) / E * E;
+    // chunk is a multiple of 8 elements and nsplit chunks cover V
+    const int v0 = head + k * chunk;
+    const int v1 = min(body_end, v0 + chunk);
+    const uint32_t abits = sizeof(T) == 2 ? (uint32_t)(uint16_t)a : __float_as_uint((float)a);
+    for (int v = v0 + threadIdx.x * E; v < v1; v += kFillThreads * E) {
+        uint32_t wd[4] = {0u, 0u, 0u, 0u};
+        const int off = pr.x - v;                       // in [0, E) if the prediction is here
+        if (off >= 0 && off < E) {
+            const int word = sizeof(T) == 2 ? off >> 1 : off;
+            const uint32_t val = sizeof(T) == 2 ? abits << ((off & 1) * 16) : abits;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) wd[i] = i == word ? val : 0u;
-            }
-            *reinterpret_cast<uint4*>(z + v) = make_uint4(wd[0], wd[1], wd[2], wd[3]);
+            for (int i = 0; i < 4; ++i) wd[i] = i == word ? val : 0u;
         }
-    } else {
-        for (int v = v0 + threadIdx.x; v < v1; v += kFillThreads)
-            z[v] = v == pr.x ? a : T(0);
+        *reinterpret_cast<uint4*>(z + v) = make_uint4(wd[0], wd[1], wd[2], wd[3]);
     }
+    const int tid = threadIdx.x;
+    if (k == 0 && tid < head) z[tid] = tid == pr.x ? a : T(0);
+    if (k == nsplit - 1 && tid < V - body_end)
+        z[body_end + tid] = body_end + tid == pr.x ? a : T(0);
 }
 
 // The top byte of a hash as k/256 in [-1/2, 1/2).
