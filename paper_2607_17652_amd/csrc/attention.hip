@@ -50,6 +50,7 @@ constexpr int kMinChunkTiles = 4;   // never split below 128 keys
 constexpr int kMaxSplits = 64;      // splits of one unit the combine can merge
 constexpr int kMaxHeadDim = 128;    // largest head_dim built (32, 64, 128)
 constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kSkippedLse = INFINITY;   // part_lse of a skipped fp32 block: no row's own is +inf
 constexpr float kRescaleSlack = 8.0f;  // lazy rescale: running max may lag by 2^8
 
 // A work item: its unit, key range and partial slot, and the request and
@@ -1350,15 +1351,15 @@ combine_kernel(PackView pv, AttnWs ws, T* __restrict__ out, int Hq, int Hkv,
                 for (int j = 0; j < 8; ++j)
                     if (k0 + j < ns) wgt[k0 + j][threadIdx.x] = l[j];
             }
+            const bool skipped = std::is_same<T, float>::value && wgt[0][threadIdx.x] == kSkippedLse;
             float den = 0.f;
             for (int k = 0; k < ns; ++k) {
                 const float w = __builtin_amdgcn_exp2f(wgt[k][threadIdx.x] - mx);
                 wgt[k][threadIdx.x] = w;
                 den += w;
             }
-            // fp32: pieces of a skipped block hold -inf (its rows stay unwritten)
-            inv_den[threadIdx.x] = std::is_same<T, float>::value && mx == -INFINITY ? -1.0f
-                                                                                    : 1.0f / den;
+            // fp32: a skipped block's rows stay unwritten (a NaN row is written)
+            inv_den[threadIdx.x] = skipped ? -1.0f : 1.0f / den;
         }
         __syncthreads();
     };
@@ -1539,7 +1540,7 @@ attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k_cache,
     const bool wave_ok = rg * kRowsPerWg + wave * 32 < bl * g;   // the wave has query rows
 
     // Every page the block reads must be valid, else the block is skipped
-    // (a split block's pieces say so to the merge with a -inf weight).
+    // (each of a split block's pieces scans them all and says so to the merge).
     __shared__ int bad_page;
     if (tid == 0) bad_page = 0;
     __syncthreads();
@@ -1554,7 +1555,7 @@ attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k_cache,
     if (bad_page || ke > kv_len) {
         if (tid == 0) record_error(pv.hdr, b, FB_DERR_PAGE);
         if (slot >= 0 && tid < kRowsPerWg)
-            ws.part_lse[(size_t)slot * kRowsPerWg + tid] = -INFINITY;
+            ws.part_lse[(size_t)slot * kRowsPerWg + tid] = kSkippedLse;
         return;
     }
 

@@ -77,3 +77,35 @@ def test_f32_bad_page_skips_the_blocks_that_read_it(prefix):
     req = step.pack.view()["row_req"]
     assert bool((step.out[req == 1] == 7.0).all())
     assert bool((step.out[(req == 0) | (req == 2)] != 7.0).any(dim=-1).all())
+
+
+def attend(step):
+    step.pack_step()
+    step.kv_step()
+    step.out.fill_(7.0)
+    step.attention_step()
+    torch.cuda.synchronize()
+    assert fb.fb_pack_read_status(step.pack)["code"] == 0
+    return step.out.clone()
+
+
+# one workgroup per unit without a plan, planned whole units, units in pieces
+FORMS = [dict(d=32, prefix=("uniform", 20, 100)), dict(prefix=("uniform", 600, 900), kv_split=2048),
+         dict(prefix=("uniform", 600, 900), kv_split=64)]
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("kw", FORMS)
+def test_f32_nan_query_rows_come_out_as_nan(kw, value):
+    """A live row whose scores are all NaN is written as NaN, in whichever
+    form; the others are as without it (up to the moment at which a wave
+    rescales its rows: a few 2^-24)."""
+    wl, host, t, step = f32(n_blocks=4, page_size=32, **kw)
+    log(f"[f32 attention] {value} in a query, {kw}")
+    ref = attend(step)
+    row = int(torch.nonzero(step.pack.view()["row_req"] == 1).flatten()[2])
+    t["q"][row, 1, 5] = value
+    out = attend(step)
+    assert bool(torch.isnan(out[row, 1]).all())
+    out[row, 1] = ref[row, 1]
+    assert torch.allclose(out, ref, rtol=1e-5, atol=1e-6)
