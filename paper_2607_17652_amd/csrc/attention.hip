@@ -27,6 +27,8 @@
 //   combine        merges split partials with their log-sum-exp weights,
 //                  walking the plan's list of split units
 //   attn_f32       the same items in fp32 on v_mfma_f32_32x32x2_f32
+#include <float.h>
+
 #include <type_traits>
 #include <utility>
 
@@ -1620,8 +1622,12 @@ attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k_cache,
     floatx16 o[DT];
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) o[dt] = floatx16{};
-    float m_run = -INFINITY;   // running max of scores, log2 domain (may lag by the slack)
+    // Running max of the raw scores (may lag by the slack).  Scores are scaled
+    // after it is taken off, so that none that is finite overflows; while every
+    // score of a row is -inf, 0 stands in for it and the row's sums stay 0.
+    float m_run = -INFINITY;
     float l = 0.f;             // this lane half's share of the denominator
+    const float slack = fminf(kRescaleSlack / scale_log2, FLT_MAX);
 
     load_pages(0);
     issue(0);
@@ -1656,11 +1662,12 @@ attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k_cache,
         float mx = s[0];
 #pragma unroll
         for (int x = 1; x < 16; ++x) mx = fmaxf(mx, s[x]);
-        mx = wave_xor32_max(mx) * scale_log2;
+        mx = wave_xor32_max(mx);
         // rescale only when a row's max passes the running one by the slack
-        if (__any(mx > m_run + kRescaleSlack)) {
+        if (__any(mx > m_run + slack)) {
             const float m_new = fmaxf(mx, m_run);
-            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+            const float alpha = m_run == -INFINITY
+                ? 0.f : __builtin_amdgcn_exp2f((m_run - m_new) * scale_log2);
 #pragma unroll
             for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
@@ -1668,9 +1675,10 @@ attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k_cache,
             l *= alpha;
             m_run = m_new;
         }
+        const float m_ref = m_run == -INFINITY ? 0.f : m_run;
 #pragma unroll
         for (int x = 0; x < 16; ++x)
-            s[x] = __builtin_amdgcn_exp2f(fmaf(s[x], scale_log2, -m_run));
+            s[x] = __builtin_amdgcn_exp2f((s[x] - m_ref) * scale_log2);
         float t[8];
 #pragma unroll
         for (int x = 0; x < 8; ++x) t[x] = s[x] + s[x + 8];
@@ -1703,7 +1711,8 @@ attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k_cache,
     if (!wave_ok) return;
 
     l += __shfl_xor(l, 32, 64);
-    const float inv_l = 1.0f / l;
+    // a piece whose scores are all -inf weighs nothing in the merge
+    const float inv_l = slot >= 0 && l == 0.f ? 0.f : 1.0f / l;
     if (slot < 0 && !row_ok) return;
     float* dst = slot < 0 ? out + q_off
                           : ws.part_o + ((size_t)slot * kRowsPerWg + r_local) * D;
@@ -1715,8 +1724,11 @@ attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ k_cache,
                                           o[dt][grp * 4 + 2] * inv_l, o[dt][grp * 4 + 3] * inv_l);
             *reinterpret_cast<float4*>(dst + dt * 32 + grp * 8 + h * 4) = v4;
         }
-    if (slot >= 0 && h == 0)
-        ws.part_lse[(size_t)slot * kRowsPerWg + r_local] = m_run + __log2f(l);
+    if (slot >= 0 && h == 0) {
+        float lse = fmaf(m_run, scale_log2, __log2f(l));
+        if (l > 0.f) lse = fminf(fmaxf(lse, -FLT_MAX), FLT_MAX);   // kSkippedLse is not a row's
+        ws.part_lse[(size_t)slot * kRowsPerWg + r_local] = lse;
+    }
 }
 
 }  // namespace

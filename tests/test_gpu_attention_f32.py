@@ -1,10 +1,11 @@
 """The fp32 attention's MFMA kernel at the sizes where it can go wrong: every
 head size, pages of one key (V key by key) to whole tiles and more, partial
 key and row tiles, whole and split units, and a block with a bad page."""
+import numpy as np
 import pytest
 import torch
 
-from harness import OracleCase, compare_case, gpu_results, log, setup
+from harness import ATTN_TOL, OracleCase, compare_case, gather_kv, gpu_results, log, setup
 from paper_2607_17652_amd import binding as fb
 
 pytestmark = pytest.mark.gpu
@@ -109,3 +110,42 @@ def test_f32_nan_query_rows_come_out_as_nan(kw, value):
     assert bool(torch.isnan(out[row, 1]).all())
     out[row, 1] = ref[row, 1]
     assert torch.allclose(out, ref, rtol=1e-5, atol=1e-6)
+
+
+@pytest.mark.parametrize("value", [float("-inf"), float(np.finfo(np.float32).min)])
+@pytest.mark.parametrize("masked", [range(0, 32), range(64, 192), range(0, 160)])
+@pytest.mark.parametrize("kw", [dict(d=32, prefix=("fixed", 224)),
+                                dict(d=64, prefix=("fixed", 640), kv_split=2048),
+                                dict(d=64, prefix=("fixed", 640), kv_split=64)])
+def test_f32_masked_keys(kw, masked, value):
+    """Keys put out of sight by a score of -inf or of the lowest float (one
+    head element is the mask's: 1 in the queries, the value in masked keys),
+    at a scale that takes the lowest float past the range: whole key tiles and
+    pieces weigh nothing, wherever they lie."""
+    wl, host, t, step = f32(B=2, n_blocks=4, page_size=32, prefix_jitter=0, **kw)
+    log(f"[f32 attention] keys {masked} at {value}, {kw}")
+    step.shape.sm_scale = 1.0
+    t["q"][..., 0] = 1.0
+    t["k_new"][..., 0] = 0.0
+    t["k_cache"][..., 0] = 0.0
+    pos = torch.tensor(list(masked), device="cuda")
+    for b in range(wl.B):
+        page = step.page_table[b][pos // wl.page_size].long()
+        t["k_cache"][page, :, pos % wl.page_size, 0] = value
+    out = attend(step)
+    view = step.pack.view()
+    row_req, row_pos = view["row_req"].tolist(), view["row_pos"].tolist()
+    got, q = out.double().cpu().numpy(), t["q"].double().cpu().numpy()
+    for b in range(wl.B):
+        o = int(host["o"][b])
+        K, V = gather_kv(t["k_cache"], t["v_cache"], step.page_table[b],
+                         o + int(host["w"][b]) * wl.bl, wl.page_size)
+        for r in (r for r in range(wl.row_cap) if row_req[r] == b):
+            seen = np.setdiff1d(np.arange(o + ((row_pos[r] - o) // wl.bl + 1) * wl.bl), masked)
+            for h in range(wl.Hq):
+                kh = h // (wl.Hq // wl.Hkv)
+                z = K[seen, kh] @ q[r, h]
+                p = np.exp(z - z.max())
+                ref = (p / p.sum()) @ V[seen, kh]
+                err = np.abs(got[r, h] - ref).max()
+                assert err <= ATTN_TOL["f32"], (b, r, h, err)
