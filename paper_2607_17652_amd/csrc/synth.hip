@@ -180,7 +180,11 @@ __device__ inline float embed_value(uint64_t h) {
 // per element remains, of which only the top byte is used) and successive
 // hash inputs by addition.  8192 rows of 32 + 2 x 8 heads of 128 in bf16
 // (101 MB): 32 us, was 91 with three hashes and a 2-byte store per
-// element.  EV = 1 where a buffer is not 16-byte aligned.
+// element.  EV = 1 where a buffer is not 16-byte aligned, and in bf16 where it
+// covers the row in one pass: eight hashes in a row then take longer than the
+// threads they spare (8192 rows of 96 / 128 / 192 / 256 elements, EV = 1
+// against 8: 5.3 / 5.3 / 6.3 / 7.3 us against 6.4 / 6.5 / 6.4 / 6.5; fp32,
+// against 4: 5.2 / 5.4 / 6.4 / 7.4 against 5.0 / 5.1 / 5.4 / 5.6).
 template <typename T, int EV>
 __global__ void __launch_bounds__(kEmbedThreads)
 synth_embed_kernel(PackView pv, int Hq, int Hkv, int d, uint64_t seed, T* __restrict__ q,
@@ -258,13 +262,14 @@ template <typename T>
 static void embed_rows(const fb_pack* pack, const fb_attn_shape* sh, uint64_t seed, void* q,
                        void* k_new, void* v_new, hipStream_t stream) {
     constexpr int EV = 16 / sizeof(T);
+    const int n = (sh->Hq + 2 * sh->Hkv) * sh->head_dim;
     const bool aligned = (((uintptr_t)q | (uintptr_t)k_new | (uintptr_t)v_new) & 15u) == 0;
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)pack->row_cap), dim3(kEmbedThreads), 0, stream,
                            pack_view(pack), sh->Hq, sh->Hkv, sh->head_dim, seed,
                            static_cast<T*>(q), static_cast<T*>(k_new), static_cast<T*>(v_new));
     };
-    if (aligned) launch(synth_embed_kernel<T, EV>);
+    if (aligned && (sizeof(T) == 4 || n >= kEmbedThreads)) launch(synth_embed_kernel<T, EV>);
     else launch(synth_embed_kernel<T, 1>);
 }
 

@@ -1,6 +1,7 @@
 """The synthetic embeddings' vector and single-element stores, bit for bit
 against the oracle: whole 16-byte runs per thread where every buffer is
-16-byte aligned, one element per store where one of them is not."""
+16-byte aligned and the row long enough (bf16: from 256 elements on), one
+element per store otherwise."""
 import os
 import sys
 
@@ -18,7 +19,7 @@ from paper_2607_17652_amd.runner import WavefrontStep  # noqa: E402
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("Hq,Hkv,d", [(2, 1, 32), (8, 8, 64), (32, 8, 128)])
+@pytest.mark.parametrize("Hq,Hkv,d", [(2, 1, 32), (5, 1, 32), (4, 2, 32), (8, 8, 64), (32, 8, 128)])
 @pytest.mark.parametrize("shifted", [None, "q", "v"])
 def test_embed_rows(dtype, Hq, Hkv, d, shifted):
     wl = synth.workload("single", dtype=dtype, B=3, Hq=Hq, Hkv=Hkv, d=d, bl=8,
