@@ -127,11 +127,15 @@ __device__ inline uint16_t level_value<uint16_t>(float a) {
 // stores its part of the row's 16-byte-aligned body whole, wherever the row
 // starts; the first and last split also store the few elements around the
 // body.  8192 rows in bf16: V = 157184 500 us (5.15 TB/s, the copy probe's
-// rate), 157183 534 -> 514, 50001 187 -> 180 against one element per store
-// where rows are unaligned.  64 KB a workgroup: 16 KB 546 / 552 / 184 us, whole
-// rows 490 / 524 / 181, whole rows by 1024 threads 480 / 562 / 178; nontemporal
-// stores 564 / 638 / 207.
-template <typename T>
+// rate), 157183 534 -> 514, 50001 187 -> 180, 1003 15.4 -> 15.6 against one
+// element per store where rows are unaligned.  64 KB a workgroup, which no vocabulary length
+// loses much by: 16 KB 546 / 552 / 184 us, whole rows 490 / 524 / 181, whole
+// rows by 1024 threads 480 / 562 / 178 (the best where rows are aligned, the
+// worst but one where they are not); nontemporal stores 564 / 638 / 207.
+// WHOLE: every row is a whole number of 16-byte words, so there is nothing
+// around the body; finding it out from the address costs short rows 4-7%
+// (V = 1000 bf16 14.5 -> 15.4 us, fp32 16.2 -> 16.9; no difference from 4096 on).
+template <typename T, bool WHOLE>
 __global__ void __launch_bounds__(kFillThreads)
 synth_fill_kernel(const int2* __restrict__ pred, PackView pv, int V, int nsplit, int chunk,
                   float4 levels, T* __restrict__ logits) {
@@ -144,8 +148,8 @@ synth_fill_kernel(const int2* __restrict__ pred, PackView pv, int V, int nsplit,
     const T a = level_value<T>(lf);
     T* z = logits + (size_t)row * V;
     constexpr int E = 16 / sizeof(T);
-    const int head = min(V, (int)((16 - ((uintptr_t)z & 15)) & 15) / (int)sizeof(T));
-    const int body_end = head + (V - head) / E * E;
+    const int head = WHOLE ? 0 : min(V, (int)((16 - ((uintptr_t)z & 15)) & 15) / (int)sizeof(T));
+    const int body_end = WHOLE ? V : head + (V - head) / E * E;
     // chunk is a multiple of 8 elements and nsplit chunks cover V
     const int v0 = head + k * chunk;
     const int v1 = min(body_end, v0 + chunk);
@@ -161,6 +165,7 @@ synth_fill_kernel(const int2* __restrict__ pred, PackView pv, int V, int nsplit,
         }
         *reinterpret_cast<uint4*>(z + v) = make_uint4(wd[0], wd[1], wd[2], wd[3]);
     }
+    if (WHOLE) return;
     const int tid = threadIdx.x;
     if (k == 0 && tid < head) z[tid] = tid == pr.x ? a : T(0);
     if (k == nsplit - 1 && tid < V - body_end)
@@ -249,12 +254,19 @@ hipError_t launch_synth_logits(const fb_req_state* st, const int32_t* tokens, in
     const SynthSizes z = synth_sizes(pack, V);
     const float4 lv = make_float4(m->levels[0], m->levels[1], m->levels[2], m->levels[3]);
     const dim3 grid((unsigned)pack->row_cap * (unsigned)z.nsplit);
-    if (dtype == FB_BF16)
-        hipLaunchKernelGGL(synth_fill_kernel<uint16_t>, grid, dim3(kFillThreads), 0, stream,
-                           pr, pv, V, z.nsplit, z.chunk, lv, static_cast<uint16_t*>(logits));
-    else
-        hipLaunchKernelGGL(synth_fill_kernel<float>, grid, dim3(kFillThreads), 0, stream, pr,
-                           pv, V, z.nsplit, z.chunk, lv, static_cast<float*>(logits));
+    auto fill = [&](auto kernel, auto zero) {
+        hipLaunchKernelGGL(kernel, grid, dim3(kFillThreads), 0, stream, pr, pv, V, z.nsplit,
+                           z.chunk, lv, static_cast<decltype(zero)*>(logits));
+    };
+    // the first row starts on a 16-byte boundary (checked by the callers)
+    const bool whole = (size_t)V * (dtype == FB_BF16 ? 2 : 4) % 16 == 0;
+    if (dtype == FB_BF16) {
+        if (whole) fill(synth_fill_kernel<uint16_t, true>, uint16_t());
+        else fill(synth_fill_kernel<uint16_t, false>, uint16_t());
+    } else {
+        if (whole) fill(synth_fill_kernel<float, true>, float());
+        else fill(synth_fill_kernel<float, false>, float());
+    }
     return hipGetLastError();
 }
 

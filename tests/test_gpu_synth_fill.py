@@ -16,9 +16,10 @@ from paper_2607_17652_amd.runner import WavefrontStep  # noqa: E402
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-# rows shorter than a 16-byte run, one run, remainders at both ends, the last
-# split with nothing but its tail, an aligned row length
-@pytest.mark.parametrize("V", [5, 9, 16, 1003, 32768, 32769, 65543])
+# rows shorter than a 16-byte run, one run and two, whole in fp32 alone, a
+# remainder at both ends of one split and of the first and last of several,
+# whole rows of one split and of several
+@pytest.mark.parametrize("V", [5, 9, 16, 1003, 1004, 32768, 32769, 65543, 65600])
 def test_fill_rows(dtype, V):
     wl = synth.workload("single", V=V, B=3, Hq=2, Hkv=1, d=32, bl=8,
                         window=("uniform", 1, 3), W_max=3, layout="padded")
