@@ -696,9 +696,11 @@ LmSizes lm_sizes(const fb_pack* pack, int V, int D, int cu_count) {
     // known on the device only; where the capacity allows more, the kernel
     // chooses by them, if the weight is large (from 256 MB the few-rows form is
     // 1.4-1.7x as fast where it applies) and the capacity at most 1024 rows,
-    // above which so few live ones are unlikely.
+    // above which so few live ones are unlikely.  A padded pack's rows may lie
+    // anywhere in its capacity, so that alone decides.
     const bool few = pack->row_cap <= kFewRows ||
-                     (pack->row_cap <= 8 * kFewRows && (long long)V * D >= (1LL << 27));
+                     (pack->layout != FB_PADDED && pack->row_cap <= 8 * kFewRows &&
+                      (long long)V * D >= (1LL << 27));
     z.few_rows = few ? kFewRows : 0;
     z.few_grid = few ? lm_few_parts(V, z.cu) : 0;
     const int blocks = grid > z.few_grid ? grid : z.few_grid;

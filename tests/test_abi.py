@@ -288,3 +288,19 @@ def test_noalloc_update_rejects_a_pack_above_its_array(lib):
                                        fake, fake, fake, 64, ctypes.byref(h),
                                        ctypes.byref(prm), None, None)
     assert rc == fb.FB_E_INVAL
+
+
+def test_lmhead_few_rows_form_is_not_held_for_packs_that_cannot_take_it(lib):
+    """Partials of the few-rows form (more blocks than the tile form's here)
+    are held where it may be taken: up to 128 rows, or large weights and a
+    ragged pack of up to 1024.  A padded pack above 128 rows never takes it."""
+    def size(layout, B, D):
+        pack = fb.fb_pack()
+        lib.fb_pack_init(ctypes.byref(pack), 4096, lib.fb_pack_bytes(B, 4, 32), B, 4, 32, layout)
+        return lib.fb_lmhead_workspace_bytes(ctypes.byref(pack), 157184, D)
+    for B in (2, 4, 8):
+        tiles = size(fb.FB_RAGGED, B, 64)
+        assert size(fb.FB_RAGGED, B, 2048) > tiles
+        assert size(fb.FB_PADDED, B, 2048) == size(fb.FB_PADDED, B, 64) == tiles
+    assert size(fb.FB_PADDED, 1, 2048) == size(fb.FB_RAGGED, 1, 2048)
+    assert size(fb.FB_RAGGED, 9, 2048) == size(fb.FB_RAGGED, 9, 64)
