@@ -59,11 +59,11 @@ constexpr float kRescaleSlack = 8.0f;  // lazy rescale: running max may lag by 2
 // first packed row of its tile (copied here so the attention workgroup's
 // first dependent loads are the item and then the page table).
 enum ItemField { kIUnit = 0, kIKb, kIKe, kISlot, kIB, kIRow0, kIItemInts = 8 };
-enum CountField { kCItems = 0, kCUnits, kCChunk, kCSplit };
+enum CountField { kCItems = 0, kCSplit, kCountInts = 4 };
 
 struct AttnWs {
     int32_t* items;    // [item_cap][kIItemInts]
-    int32_t* counts;   // [4]
+    int32_t* counts;   // [kCountInts]
     int4* split;       // [split_cap]: {unit, pieces, first slot, first row} of the
                        // units with more than one piece
     float* part_o;     // [slot_cap][128][D]
@@ -237,15 +237,14 @@ __device__ inline long long split_chunk(long long total_tiles, long long kt_max,
 }
 
 __global__ void __launch_bounds__(kPlanThreads)
-plan_kernel(PackView pv, AttnWs ws, int Hkv, int RG, int item_cap, int slot_cap,
-            int split_cap, int target_items, int fixed_chunk_tiles, long long max_keys) {
+plan_kernel(PackView pv, AttnWs ws, int Hkv, int RG, int item_cap, int split_cap,
+            int target_items, int fixed_chunk_tiles, long long max_keys) {
     __shared__ long long sum_lds[2][kPlanWaves];
     __shared__ int scan_lds[kPlanWaves + 1];
     __shared__ int3 trio_lds[kPlanWaves];
     __shared__ int bucket[kLenBuckets];
     const int n_tiles = pv.hdr[kHdrTiles];
     const int per_tile = Hkv * RG;
-    const int n_units = n_tiles * per_tile;
     const int n_rounds = (n_tiles + kPlanThreads - 1) / kPlanThreads;
 
     // this thread's first kPlanCache tiles, read once; kept in LDS (a
@@ -280,8 +279,6 @@ plan_kernel(PackView pv, AttnWs ws, int Hkv, int RG, int item_cap, int slot_cap,
         if (threadIdx.x == 0) {
             record_error(pv.hdr, pv.tiles[kTB], FB_DERR_PAGE);
             ws.counts[kCItems] = 0;
-            ws.counts[kCUnits] = 0;
-            ws.counts[kCChunk] = -1;
             ws.counts[kCSplit] = 0;
         }
         return;
@@ -411,8 +408,6 @@ plan_kernel(PackView pv, AttnWs ws, int Hkv, int RG, int item_cap, int slot_cap,
     }
     if (threadIdx.x == 0) {
         ws.counts[kCItems] = items_before < item_cap ? items_before : item_cap;
-        ws.counts[kCUnits] = n_units;
-        ws.counts[kCChunk] = chunk < (1 << 30) / kKeyTile ? chunk * kKeyTile : -1;   // keys
         ws.counts[kCSplit] = split_before < split_cap ? split_before : split_cap;
     }
 }
@@ -1763,7 +1758,7 @@ AttnPlanSizes attention_sizes(const fb_pack* pack, const fb_attn_shape* sh,
         return at;
     };
     z.off_items = take((size_t)z.item_cap * kIItemInts * sizeof(int32_t));
-    z.off_counts = take(4 * sizeof(int32_t));
+    z.off_counts = take(kCountInts * sizeof(int32_t));
     z.off_split = take((size_t)z.split_cap * sizeof(int4));
     if (!f32 || !f32_direct(sh)) {
         z.off_part_o = take((size_t)z.slot_cap * kRowsPerWg * D * sizeof(float));
@@ -1793,8 +1788,8 @@ static void launch_plan(const fb_pack* pack, const fb_attn_shape* sh, const Attn
     const int fixed_chunk = sh->kv_split > 0 ? sh->kv_split / kKeyTile : 0;
     const long long max_keys = (long long)sh->max_pages * sh->page_size;
     hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(kPlanThreads), 0, stream, pack_view(pack), ws,
-                       sh->Hkv, z.row_groups, z.item_cap, z.slot_cap, z.split_cap,
-                       z.target_items, fixed_chunk, max_keys);
+                       sh->Hkv, z.row_groups, z.item_cap, z.split_cap, z.target_items,
+                       fixed_chunk, max_keys);
 }
 
 hipError_t launch_attention_plan(const fb_pack* pack, const fb_attn_shape* sh, void* wsp,
