@@ -1,7 +1,8 @@
 """The window prologue where its loads change form: fewer pair groups than
 threads, a last round that is partly filled, several rounds, a head group that
-is no power of two, one-position blocks, and inputs beyond the size from which
-they are read with the streaming hint.  Every live row against the rotation in
+is no power of two, one-position blocks, inputs beyond the size from which
+they are read with the streaming hint, and more tiles than a grid's second
+extent.  Every live row against the rotation in
 float64; values and positions outside the windows exactly."""
 import numpy as np
 import pytest
@@ -41,6 +42,7 @@ def _close(got, x, pos, dtype):
     ("bf16", 2, 16, 2, 128, 128, 2),    # eight rounds, two of keys
     ("f32", 256, 32, 8, 128, 16, 4),    # 403 MB of inputs: streaming loads
     ("bf16", 256, 32, 8, 128, 32, 4),   # 403 MB
+    ("bf16", 1025, 2, 2, 32, 1, 64),    # 65600 tiles: past a grid's second extent, tiles first
 ])
 def test_prologue_forms(dtype, B, Hq, Hkv, d, bl, W):
     log(f"[prologue] {dtype} B={B} Hq={Hq} Hkv={Hkv} d={d} bl={bl}")
