@@ -38,6 +38,7 @@ def past_windows(host, wl, page_table, value, *caches):
     dict(d=128, Hq=8, Hkv=1, bl=17, page_size=16, W_max=4, window=("fixed", 4)),   # 136 rows
     dict(d=128, prefix=("uniform", 1500, 1600), kv_split=32, B=1),   # one key tile per piece
     dict(d=32, Hq=4, Hkv=4, prefix=("uniform", 3000, 4000), B=2),
+    dict(d=64, Hq=4, Hkv=2, bl=8, page_size=2, prefix=("uniform", 900, 1000)),   # split, V by key
 ])
 def test_f32_attention(kw):
     kw = dict(kw)
