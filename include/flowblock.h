@@ -283,7 +283,10 @@ size_t fb_attention_workspace_bytes(const fb_pack* pack, const fb_attn_shape* sh
  *   q, out  [row_cap][Hq][d];  caches and page_table as above
  *   ws      device workspace of fb_attention_workspace_bytes bytes
  * Rows that are not live are not written.  Deterministic: no atomics on
- * outputs, so repeated calls give bit-identical results. */
+ * outputs, so repeated calls give bit-identical results.  With kv_split = 0 the
+ * split, and so the rounding of a request's rows, goes by the whole pack, in
+ * both dtypes; a fixed kv_split that fits the workspace makes it the request's
+ * own. */
 int fb_wavefront_attention(const void* q, const void* k_cache,
                            const void* v_cache, const int32_t* page_table,
                            const fb_pack* pack, const fb_attn_shape* sh,
@@ -376,7 +379,12 @@ size_t fb_lmhead_workspace_bytes(const fb_pack* pack, int V, int D);
  * workspace `upd_ws` in the form fb_denoise_apply reads, so
  * fb_lmhead_reduce + fb_denoise_apply is fb_denoise_update on logits that
  * never exist.  The logits are accumulated in float32 (MFMA bf16 products),
- * so they may differ from an exact product by the accumulation error.
+ * so they may differ from an exact product by the accumulation error.  The
+ * order of the sum goes by the form the call takes: one for packs of at most
+ * 128 rows (and ragged ones of up to 1024 with at most 128 live and a large
+ * weight), another for the rest.  So a row's logits may differ in float32
+ * rounding, and x_hat at a near tie, between packs; within a call equal rows
+ * of weight tie exactly.
  *   hidden  bf16 [row_cap][D] (the packed rows' final hidden states)
  *   weight  bf16 [V][D] (one row per vocabulary id)
  *   D       a multiple of 64; V * D and row_cap * D below 2^30

@@ -42,11 +42,16 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int kRowsPerWg = 128;     // 4 waves x 32 query rows
 constexpr int kAttnThreads = 256;
-constexpr int kWgsPerCu = 3;          // resident attention workgroups per CU
+constexpr int kWgsPerCu = 3;          // attention workgroups per CU aimed at (resident at D = 128)
 constexpr int kKeyTile = 32;
-constexpr int kF32WgsPerCu = 2;       // resident fp32 workgroups per CU
-// keys * head_dim that one fp32 workgroup walks without a plan: a key tile
-// takes it about D/32 us, the plan and the merge about 16
+constexpr int kF32WgsPerCu = 2;       // the same in fp32
+// keys * head_dim of the cache that one fp32 workgroup walks without a plan: a
+// key tile takes it about D/32 us.  The line was drawn with a plan and a merge
+// of about 16 us on the other side.  Packs of at most 64 tiles have no plan
+// kernel since, and a shorter merge; against that (4 requests of 2 blocks) the
+// whole unit still wins at 160 keys (d = 64: 14.7 us, split 17.1; d = 128: 24.4,
+// 26.9) and loses further on (288 keys, d = 64: 24.9, 19.3; d = 32: 16.0, 14.2;
+// 544 keys, d = 32: 28.4, 14.6).
 constexpr long long kF32DirectWork = 32768;
 constexpr int kMinChunkTiles = 4;   // never split below 128 keys
 constexpr int kMaxSplits = 64;      // splits of one unit the combine can merge
@@ -1292,7 +1297,8 @@ __device__ inline void store_out4<float>(float* p, const float4& v) {
 // so a workgroup takes few rows (one column group per thread); with many, by
 // the workgroups launched (most find no split unit).  Kernel trace, R = 32 / 16
 // / 8: 12 units in nine pieces 8.6 / 6.3 / 5.5 us; 128 (fp32) 9.1 / 8.5 / 10.9;
-// 256 15.1 / 14.4 / 19.2; 576 with few split 6.6 / 7.3 / 15.0; 768 5.2 / 5.2 / 8.9.
+// 256 15.1 / 14.4 / 19.2; 576 with few split 6.6 / 7.3 / 15.0; 768 with hardly
+// any split 5.2 / 5.2 / 8.9.  (768 with a good part split, only R = 32: 10.1.)
 template <typename T, int R, int IF>
 __global__ void __launch_bounds__(kAttnThreads)
 combine_kernel(PackView pv, AttnWs ws, T* __restrict__ out, int Hq, int Hkv,
@@ -1462,9 +1468,9 @@ combine_kernel(PackView pv, AttnWs ws, T* __restrict__ out, int Hq, int Hkv,
 // caches too short to be worth splitting).  INLINE as in the bf16 kernel.
 //
 // Measured (8 requests of 256-2048 prefix keys, 16/4 heads, d = 128: 6.4
-// GFLOP, 42 us at the 154 TFLOP/s of a large fp32 matrix product): the whole
-// call takes 86 us with the plan and the merge, against 15.8 ms for one key
-// per lane on the vector units with K rows read a lane apart.
+// GFLOP, 41 us at the nominal 157 TFLOP/s): the whole call, kernel and merge,
+// takes 68-96 us by the lengths, against 15-16 ms for one key per lane on the
+// vector units with K rows read a lane apart.
 template <int D>
 struct F32Tile {
     static constexpr int kCpr = D / 4;                      // 16-byte chunks of a K row
@@ -1741,10 +1747,12 @@ AttnPlanSizes attention_sizes(const fb_pack* pack, const fb_attn_shape* sh,
     z.rows_per_unit = pack->bl * g;
     z.row_groups = (z.rows_per_unit + kRowsPerWg - 1) / kRowsPerWg;
     z.unit_cap = pack->tile_cap * sh->Hkv * z.row_groups;
-    // One item per workgroup the chip holds at once (kWgsPerCu per CU in bf16,
-    // kF32WgsPerCu in fp32): more splits cost more in partial writes, the
-    // merge and per-item start-up than they win in balance (measured in bf16:
-    // 8 per CU was 2-25% slower).
+    // One item per workgroup the chip holds at once at D = 128 (kWgsPerCu per
+    // CU in bf16, kF32WgsPerCu in fp32): more splits cost more in partial
+    // writes, the merge and per-item start-up than they win in balance
+    // (measured in bf16 at D = 128: 8 per CU was 2-25% slower).  Smaller heads
+    // aim at the same number, though a CU holds more of them at once (by
+    // registers and LDS: bf16 four at 64 and five at 32, fp32 three and four).
     const bool f32 = sh->dtype == FB_F32;
     z.target_items = (f32 ? kF32WgsPerCu : kWgsPerCu) * (cu_count > 0 ? cu_count : 256);
     z.item_cap = z.unit_cap + z.target_items;

@@ -105,12 +105,17 @@ __device__ inline int lm_parts_dev(int n_lt, int nv, int cu) {
 // takes the second half first: with every CU at the same K offset the 128-byte
 // pieces read at one time fall on few memory channels where D is a power of
 // two.  The sum of two is the same in either order, so a row of W gives the
-// same logit in any workgroup (equal rows tie exactly).
+// same logit in any workgroup (equal rows tie exactly).  It is not the sum of
+// the 256-token form, which takes K in one chain: a row's logits may differ by
+// float32 rounding with the form that its pack gets.
 //
 // Measured (96 rows, V = 157184, D = 2048: 644 MB of W, 92 us at the read
 // probe's 7.06 TB/s): 180-198 us with the 256-token
-// tile, 112 us here (64 rows: 190 -> 111 us for the whole call; all workgroups
-// starting K together and without the nontemporal hint: 145-150 us).
+// tile, 106-111 us here (64 rows: 190 -> 111 us for the whole call; all workgroups
+// starting K together and without the nontemporal hint: 145-150 us).  From 129
+// rows on it is the 256-token tile again (160 rows 198 us, 256 rows 205): here 256
+// tokens would take 128 accumulators and as many for the second sum of K, all
+// of a wave's registers.
 __host__ __device__ inline int lm_few_parts(int V, int cu) {
     const int groups = (V + 31) / 32;
     return groups < cu ? groups : cu;

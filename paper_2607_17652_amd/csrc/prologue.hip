@@ -93,13 +93,14 @@ __device__ inline void rotate8(float (&lo)[8], float (&hi)[8], const float2* cs)
 // needs: the first round's loads in flight while the table is worked out; the
 // KV heads of one block side by side in the grid, so that the workgroups at
 // work together walk whole rows instead of one head's 1 KB in every 8; and, NT,
-// the nontemporal hint where the inputs cannot have stayed in the 256 MB
-// memory-side cache (smaller inputs that their producer just wrote are served
-// from it, and the hint then costs up to half).  256 requests, 20416 live rows
-// of 32 + 2 x 8 heads of 128 in bf16 (502 MB): 108-115 us before, 97 with the
-// loads and the order (100 the order alone), 81 with the hint = 6.2 TB/s (95
-// where the inputs differ from call to call).  16384 rows of 16 + 2 x 2 heads:
-// 26.6 us, with the hint 31.5.
+// the nontemporal hint where the inputs are larger than the 256 MB memory-side
+// cache.  256 requests, 20416 live rows of 32 + 2 x 8 heads of 128 in bf16 (502
+// MB): 111 us before, 100 now on inputs that change from call to call, 80 =
+// 6.2 TB/s on the same ones again.  The hint is for inputs that come from
+// memory: the first call on new ones takes 125 us with it and 148 without.
+// Calls back to back on changing inputs lose 2.5% by it (97 us without), and
+// smaller inputs, served from the cache, up to a fifth (16384 rows of 16 + 2 x 2
+// heads: 26.6 us, with the hint 31.5).
 template <typename T, bool NT>
 __global__ void __launch_bounds__(kRopeThreads)
 rope_kv_kernel(const T* __restrict__ q_in, T* __restrict__ q_out, const T* __restrict__ k_new,
@@ -303,6 +304,11 @@ hipError_t launch_window_prologue(const void* q_in, void* q_out, const void* k_n
     // a grid's second extent ends at 65535: packs of more tiles go tiles first
     const dim3 grid = pack->tile_cap <= 65535 ? dim3(sh->Hkv, pack->tile_cap)
                                               : dim3(pack->tile_cap, sh->Hkv);
+    // NT goes by the capacity, as the live rows are known on the device only.  A
+    // capacity of 32768 rows (403 MB of inputs) with few of them live, us with the
+    // hint and without: 512 rows 7.7 / 7.6, 2048 13.2 / 12.7, 8192 38 / 44, 16384
+    // 81 / 79; on new inputs 33 / 30, 38 / 36, 59 / 84, 93 / 118; right behind the
+    // kernels that write them it costs 0-2.5.
     const size_t elt = sh->dtype == FB_BF16 ? 2 : 4;
     const bool nt = (size_t)pack->row_cap * (sh->Hq + 2 * sh->Hkv) * D * elt > kCacheBytes;
     auto go = [&](auto kernel, auto zero) {
